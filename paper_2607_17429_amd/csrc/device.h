@@ -1,6 +1,6 @@
 // Device helpers shared by the sector, block and H.V kernels: packed state
 // labels, sector rank / unrank over digit-sum count tables, successor in
-// label order, and the orbit search.
+// label order, and the orbit search (candidate sets over the group).
 //
 // A packed label stores site k's digit a_k = m_k + s in bits [k*b, k*b+b),
 // b = ceil(log2(2s+1)).  Comparing packed labels as integers gives the same
@@ -49,6 +49,15 @@ __host__ __device__ __forceinline__ bool padded_rep_of(const PadMap& m, uint64_t
   return slot < m.rpl && i < m.n_reps;
 }
 
+// One word of the rank lookup: bit k is set when rank 64 w + k is a
+// representative, base counts the representatives before the word.  One
+// 16-byte record, because a lookup is a random access: bits and base in
+// arrays of their own cost two lines each.
+struct alignas(16) RankWord {
+  uint64_t bits;
+  uint32_t base, unused;
+};
+
 template <typename W>
 __device__ __forceinline__ int digit(W x, int k, int b, W mask) {
   return (int)((x >> (k * b)) & mask);
@@ -59,9 +68,23 @@ __device__ __forceinline__ int digit(W x, int k, int b, W mask) {
 template <typename W>
 __device__ __forceinline__ uint64_t sector_rank(W x, int N, int b, int d, int A, const uint64_t* cnt,
                                                 int stride) {
-  const W mask = (W(1) << b) - 1;
   uint64_t r = 0;
   int rem = A;
+  if (b == 1) {
+    // one term per set bit, highest first, four table reads in flight
+    for (; rem > 0; rem -= 4) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool on = x != 0 && rem > q;
+        const int pos = on ? (int)(8 * sizeof(W)) - 1 - (sizeof(W) == 8 ? __clzll((long long)x) : __clz((int)x)) : 0;
+        const uint64_t c = cnt[on ? pos * stride + rem - q : 0];
+        r += on ? c : 0;
+        x &= ~(W(on) << pos);
+      }
+    }
+    return r;
+  }
+  const W mask = (W(1) << b) - 1;
   for (int pos = N - 1; pos >= 0; --pos) {
     int a = digit(x, pos, b, mask);
     for (int t = 0; t < a; ++t) {
@@ -130,125 +153,296 @@ __device__ __forceinline__ W sector_next(W x, int N, int b, int d) {
   return x;  // x was the largest label of the sector
 }
 
-// Image of x under group element g through 4-bit chunk tables:
-// tab[(g * NCH + c) * 16 + v] = packed image of chunk value v at chunk c.
-template <typename W, int NCH>
-__device__ __forceinline__ W permute(const W* __restrict__ tab, int g, const int* off) {
-  const W* t = tab + (size_t)g * (NCH * 16);
-  W img = 0;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) img |= t[off[c]];
-  return img;
-}
-
-template <typename W, int NCH>
-__device__ __forceinline__ void chunk_offsets(W a, int* off) {
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) off[c] = c * 16 + (int)((a >> (4 * c)) & W(15));
-}
-
-// Chunk tables of a factored group G = T H (every g = t h exactly once):
-// the tables of the |H| elements, then those of the |T| elements, then
-// gidx[t * |H| + h] = index of t h (uint16).  With H = {e} the T tables are
-// those of every element in index order.
-template <typename W, int NCH>
-struct OrbitTabs {
-  const W* H;
-  const W* T;
-  const uint16_t* gidx;
-  int nH, nT;
+// ---- orbit search ------------------------------------------------------------
+// The orbit minimum of a label x is found bit by bit from the top: a set of
+// candidate elements starts as the whole group, and at each image bit the
+// candidates whose image has a 0 there stay (all stay when none has a 0).
+// What is left maps x to the smallest image, and the lowest index in the set
+// is the smallest element reaching it.  The set is a bit mask of GW 64-bit
+// words (GW = 2, 5, 16 for groups of up to 128, 320, 1024 elements), and the
+// set of elements with a 1 at an image bit is the OR of one mask per 4-site
+// chunk of x: each position halves the candidates, so about log2 |G| + 2
+// positions of N/4 mask lookups replace the |G| images of N b / 4 lookups
+// each that a walk over the group costs (icosidodecahedron: about 10 x 8
+// 16-byte reads instead of 130 x 8 4-byte ones).
+//
+// For labels of b > 1 bits per site the masks are those of the sites: the bit
+// plane of digit bit `sub` (site s's bit at position s) is looked up.
+//
+// Mask table: mask[((p * NC + c) * 16 + v) * GW + w], p = 0 for the highest
+// site, NC = chunks of 4 sites.  The first n_lds positions are read from LDS
+// (lds), the others from memory (mask).  Image tables of the factored group G = T H (every g =
+// t h exactly once): img[(row * nch + c) * 16 + v] = image of value v of the
+// 4-bit chunk c of a label, rows = the |H| elements, then the |T| elements;
+// split[g] = t << 16 | h.  PLAIN: one bit per site and no spin flip (every
+// s = 1/2 sector but the flip-resolved ones), known at compile time.
+template <typename W, int GW, bool PLAIN>
+struct Orbit {
+  const uint64_t* mask;
+  const uint64_t* lds;
+  int n_lds;
+  const W* img;
+  const uint32_t* split;
+  int nH, nch, NC, N, b, G;
+  bool zf_;  // resolve by the spin flip too (G x Z2)
+  W full;    // packed label with every digit d - 1 (F x = full - x)
+  __device__ __forceinline__ bool zf() const { return !PLAIN && zf_; }
+  __device__ __forceinline__ int bits() const { return PLAIN ? 1 : b; }
 };
 
-template <typename W, int NCH>
-__device__ __forceinline__ OrbitTabs<W, NCH> orbit_tabs(const W* tab, int nH, int nT) {
-  OrbitTabs<W, NCH> o;
-  o.H = tab;
-  o.T = tab + (size_t)nH * NCH * 16;
-  o.gidx = reinterpret_cast<const uint16_t*>(tab + (size_t)(nH + nT) * NCH * 16);
-  o.nH = nH;
-  o.nT = nT;
-  return o;
+// Image of x under the group element of table row `row` (a lane's own row).
+template <typename W>
+__device__ __forceinline__ W image_row(const W* __restrict__ img, int nch, int row, W x) {
+  const W* t = img + (size_t)row * (nch * 16);
+  W y = 0;
+#pragma unroll 4
+  for (int c = 0; c < nch; ++c) y |= t[c * 16 + (int)((x >> (4 * c)) & W(15))];
+  return y;
 }
 
-// Orbit minimum and the smallest group index h reaching it (U(h) a = best).
-// Every lane of the wave walks the (h, t) pairs in the same order, so the
-// table reads of one step hit at most 16 distinct words per chunk; ties on
-// the image are broken by the group index, so the result does not depend on
-// the walk order.
-template <typename W, int NCH>
-__device__ __forceinline__ void canon_min(W a, const OrbitTabs<W, NCH>& o, W& best, int& bestg) {
-  int offa[NCH];
-  chunk_offsets<W, NCH>(a, offa);
-  best = a;
-  bestg = 0;
-  for (int hi = 0; hi < o.nH; ++hi) {
-    int off[NCH];
-    if (hi == 0) {
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ W image(const Orbit<W, GW, PLAIN>& o, int g, W x) {
+  const uint32_t th = o.split[g];
+  if (o.nH > 1) x = image_row<W>(o.img, o.nch, (int)(th & 0xffffu), x);
+  return image_row<W>(o.img, o.nch, o.nH + (int)(th >> 16), x);
+}
+
+// The bits `sub` of every digit of x, site s's at position s.
+template <typename W>
+__device__ __forceinline__ W digit_plane(W x, int N, int b, int sub) {
+  if (b == 1) return x;
+  if (b == 2) {
+    uint64_t y = ((uint64_t)x >> sub) & 0x5555555555555555ull;
+    y = (y | (y >> 1)) & 0x3333333333333333ull;
+    y = (y | (y >> 2)) & 0x0f0f0f0f0f0f0f0full;
+    y = (y | (y >> 4)) & 0x00ff00ff00ff00ffull;
+    y = (y | (y >> 8)) & 0x0000ffff0000ffffull;
+    y = (y | (y >> 16)) & 0x00000000ffffffffull;
+    return (W)y;
+  }
+  W y = 0;
+  for (int k = 0; k < N; ++k) y |= ((x >> (k * b + sub)) & W(1)) << k;
+  return y;
+}
+
+// The planes of a label: kept for b <= 2, formed on use above.
+template <typename W>
+struct Planes {
+  W x, p0, p1;
+  int N, b;
+  __device__ __forceinline__ Planes(W x_, int N_, int b_) : x(x_), N(N_), b(b_) {
+    p0 = digit_plane<W>(x, N, b, 0);
+    p1 = b == 2 ? digit_plane<W>(x, N, b, 1) : W(0);
+  }
+  __device__ __forceinline__ W of(int sub) const {
+    return b <= 2 ? (sub ? p1 : p0) : digit_plane<W>(x, N, b, sub);
+  }
+};
+
+// Elements whose image has a 1 at the plane's bit of position p's site.
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ void ones_at(const Orbit<W, GW, PLAIN>& o, W plane, int p, uint64_t (&ones)[GW]) {
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) off[c] = offa[c];
-    } else {
-      chunk_offsets<W, NCH>(permute<W, NCH>(o.H, hi, offa), off);
+  for (int w = 0; w < GW; ++w) ones[w] = 0;
+  auto gather = [&](const uint64_t* t) {
+    int c = 0;
+    for (; c + 4 <= o.NC; c += 4) {  // four lookups in flight
+      const uint64_t* e[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[q] = t + ((c + q) * 16 + (int)((plane >> (4 * (c + q))) & W(15))) * GW;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) ones[w] |= (e[0][w] | e[1][w]) | (e[2][w] | e[3][w]);
     }
-    for (int ti = hi == 0 ? 1 : 0; ti < o.nT; ++ti) {
-      const W img = permute<W, NCH>(o.T, ti, off);
-      if (img <= best) {
-        const int g = o.gidx[ti * o.nH + hi];
-        if (img < best || g < bestg) {
-          best = img;
-          bestg = g;
-        }
+    for (; c < o.NC; ++c) {
+      const uint64_t* e = t + (c * 16 + (int)((plane >> (4 * c)) & W(15))) * GW;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) ones[w] |= e[w];
+    }
+  };
+  const size_t at = (size_t)p * o.NC * 16 * GW;
+  if (p < o.n_lds)
+    gather(o.lds + at);
+  else
+    gather(o.mask + at);
+}
+
+template <int GW>
+__device__ __forceinline__ void all_elements(int G, uint64_t (&c)[GW]) {
+#pragma unroll
+  for (int w = 0; w < GW; ++w) {
+    const int n = G - 64 * w;
+    c[w] = n >= 64 ? ~0ull : n > 0 ? (1ull << n) - 1 : 0;
+  }
+}
+
+template <int GW>
+__device__ __forceinline__ int count(const uint64_t (&c)[GW]) {
+  int n = 0;
+#pragma unroll
+  for (int w = 0; w < GW; ++w) n += __popcll(c[w]);
+  return n;
+}
+
+// cand &= keep where that leaves any candidate
+template <int GW>
+__device__ __forceinline__ void keep_if_any(uint64_t (&cand)[GW], const uint64_t (&ones)[GW], bool of_ones) {
+  uint64_t any = 0;
+#pragma unroll
+  for (int w = 0; w < GW; ++w) any |= cand[w] & (of_ones ? ones[w] : ~ones[w]);
+  if (any) {
+#pragma unroll
+    for (int w = 0; w < GW; ++w) cand[w] &= of_ones ? ones[w] : ~ones[w];
+  }
+}
+
+// Removes and returns the lowest element of a non-empty set.
+template <int GW>
+__device__ __forceinline__ int pop_lowest(uint64_t (&c)[GW]) {
+  int g = 0;
+  bool found = false;
+#pragma unroll
+  for (int w = 0; w < GW; ++w)
+    if (!found && c[w]) {
+      g = 64 * w + __builtin_ctzll(c[w]);
+      c[w] &= c[w] - 1;
+      found = true;
+    }
+  return g;
+}
+
+// Orbit minimum over G (over G x Z2 with zf) and the smallest group index h
+// reaching it (U(h) a = best; index of (g, f) is f |G| + g).  Lanes that are
+// not live do no search.  ties counts the elements that reach it, which is the
+// order of the minimum's stabilizer.  The walk over positions stops when no lane of the
+// wave has more than two candidates; those left are compared as images, the
+// lowest index first, so ties (non-trivial stabilizers) go to it as well.
+// The spin flip F reverses label order (F x = full - x), so the flipped
+// images' minimum is F of the G-orbit maximum: a second set keeps that one,
+// and a G-element wins a tie with a flipped one.
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ void orbit_min(W a, bool live, const Orbit<W, GW, PLAIN>& o, W& best, int& bestg, int& ties) {
+  uint64_t lo[GW], hi[GW];
+  all_elements<GW>(o.G, lo);
+#pragma unroll
+  for (int w = 0; w < GW; ++w) {
+    if (!live) lo[w] = w == 0 ? 1 : 0;
+    hi[w] = o.zf() ? lo[w] : 0;
+  }
+  const Planes<W> planes(a, o.N, o.bits());
+  auto wide = [&] { return o.zf() ? max(count<GW>(lo), count<GW>(hi)) > 2 : count<GW>(lo) > 2; };
+  bool more = __any(wide());
+  for (int p = 0; p < o.N && more; ++p)
+    for (int sub = o.bits() - 1; sub >= 0 && more; --sub) {
+      uint64_t ones[GW];
+      ones_at<W, GW, PLAIN>(o, planes.of(sub), p, ones);
+      keep_if_any<GW>(lo, ones, false);
+      if (o.zf()) keep_if_any<GW>(hi, ones, true);
+      more = __any(wide());
+    }
+  best = ~W(0);
+  bestg = 0;
+  ties = 0;
+  for (int n = count<GW>(lo); __any(n > 0); --n)
+    if (n > 0) {
+      const int g = pop_lowest<GW>(lo);
+      const W y = image<W, GW, PLAIN>(o, g, a);
+      if (ties == 0 || y < best) {
+        best = y;
+        bestg = g;
+        ties = 0;
       }
+      ties += y == best;
     }
-  }
-}
-
-// Orbit minimum over G x Z2 (spin flip F, which reverses label order: F x =
-// full - x for packed labels).  The images of the flipped elements (g, 1) are
-// F(U(g) a), whose minimum is F of the G-orbit maximum, so one walk keeps the
-// minimum and the maximum, each with the smallest index reaching it.  Index
-// of (g, f) is f |G| + g, and ties on the label go to the smaller index, so a
-// G-element wins a tie with a flipped one.  zf = 0 gives canon_min.
-template <typename W, int NCH>
-__device__ __forceinline__ void canon_min_z(W a, const OrbitTabs<W, NCH>& o, bool zf, W full, int G, W& best,
-                                            int& bestg) {
-  if (!zf) {
-    canon_min<W, NCH>(a, o, best, bestg);
-    return;
-  }
-  int offa[NCH];
-  chunk_offsets<W, NCH>(a, offa);
-  best = a;
-  bestg = 0;
-  W top = a;
-  int topg = 0;
-  for (int hi = 0; hi < o.nH; ++hi) {
-    int off[NCH];
-    if (hi == 0) {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) off[c] = offa[c];
-    } else {
-      chunk_offsets<W, NCH>(permute<W, NCH>(o.H, hi, offa), off);
-    }
-    for (int ti = hi == 0 ? 1 : 0; ti < o.nT; ++ti) {
-      const W img = permute<W, NCH>(o.T, ti, off);
-      if (img <= best || img >= top) {
-        const int g = o.gidx[ti * o.nH + hi];
-        if (img < best || (img == best && g < bestg)) {
-          best = img;
-          bestg = g;
-        }
-        if (img > top || (img == top && g < topg)) {
-          top = img;
+  if (o.zf()) {
+    W top = 0;
+    int topg = 0, top_ties = 0;
+    for (int n = count<GW>(hi); __any(n > 0); --n)
+      if (n > 0) {
+        const int g = pop_lowest<GW>(hi);
+        const W y = image<W, GW, PLAIN>(o, g, a);
+        if (top_ties == 0 || y > top) {
+          top = y;
           topg = g;
+          top_ties = 0;
         }
+        top_ties += y == top;
       }
+    if (o.full - top < best) {
+      best = o.full - top;
+      bestg = o.G + topg;
+      ties = top_ties;
+    } else if (o.full - top == best) {
+      ties += top_ties;
     }
   }
-  const W ftop = full - top;
-  if (ftop < best) {
-    best = ftop;
-    bestg = G + topg;
-  }
+}
+
+// Whether x is the smallest label of its orbit (over G x Z2 with zf).  lo
+// holds the elements whose image agrees with x so far, hi those whose image
+// agrees with F x: x is not minimal once one of lo has a 0 where x has a 1,
+// or one of hi a 1 where F x has a 0 (its flipped image is then below x).
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ bool is_orbit_min(W x, bool live, const Orbit<W, GW, PLAIN>& o) {
+  uint64_t lo[GW], hi[GW];
+  all_elements<GW>(o.G, lo);
+#pragma unroll
+  for (int w = 0; w < GW; ++w) hi[w] = o.zf() ? lo[w] : 0;
+  const W fx = o.full - x;
+  const Planes<W> planes(x, o.N, o.bits());
+  bool open = live, minimal = live;
+  for (int p = 0; p < o.N && __any(open); ++p)
+    for (int sub = o.bits() - 1; sub >= 0 && __any(open); --sub) {
+      uint64_t ones[GW];
+      ones_at<W, GW, PLAIN>(o, planes.of(sub), p, ones);
+      const int bit = (o.N - 1 - p) * o.bits() + sub;
+      const bool xb = (x >> bit) & 1, fb = (fx >> bit) & 1;
+      uint64_t below = 0;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) {
+        if (xb)
+          below |= lo[w] & ~ones[w];
+        else
+          lo[w] &= ~ones[w];
+        if (o.zf()) {
+          if (!fb)
+            below |= hi[w] & ones[w];
+          else
+            hi[w] &= ones[w];
+        }
+      }
+      if (below) minimal = open = false;
+      // only the identity (bit 0) follows x and nothing follows F x: no smaller image is left
+      uint64_t rest = lo[0] & ~1ull;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) rest |= hi[w] | (w ? lo[w] : 0);
+      if (!rest) open = false;
+    }
+  return minimal;
+}
+
+// The elements that map x to itself (lo) and, with zf, to F x (hi).
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ void stabilizer(W x, bool live, const Orbit<W, GW, PLAIN>& o, uint64_t (&lo)[GW],
+                                           uint64_t (&hi)[GW]) {
+  all_elements<GW>(o.G, lo);
+#pragma unroll
+  for (int w = 0; w < GW; ++w) hi[w] = o.zf() ? lo[w] : 0;
+  const W fx = o.full - x;
+  const Planes<W> planes(x, o.N, o.bits());
+  bool open = live;
+  for (int p = 0; p < o.N && __any(open); ++p)
+    for (int sub = o.bits() - 1; sub >= 0 && __any(open); --sub) {
+      uint64_t ones[GW];
+      ones_at<W, GW, PLAIN>(o, planes.of(sub), p, ones);
+      const int bit = (o.N - 1 - p) * o.bits() + sub;
+      const bool xb = (x >> bit) & 1, fb = (fx >> bit) & 1;
+#pragma unroll
+      for (int w = 0; w < GW; ++w) {
+        lo[w] &= xb ? ones[w] : ~ones[w];
+        if (o.zf()) hi[w] &= fb ? ones[w] : ~ones[w];
+      }
+      if (count<GW>(lo) <= 1 && count<GW>(hi) == 0) open = false;
+    }
 }
 
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {

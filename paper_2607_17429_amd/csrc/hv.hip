@@ -266,16 +266,15 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   c.grid = hv_grid(b, L);
   c.otf = otf;
   c.wide = s.wide;
-  c.nch = s.nch;
+  c.gw = s.gw;
   c.vpl = L.VPL;
   // kernels specialised for the dense gather (table-driven H.V only)
   c.contig = pad && !otf && b.dg == b.dgp && nvec == L.tile_w * L.tiles;
-  const uint64_t tab_words = s.tab_words;
-  const uint64_t tab_bytes = tab_words * (s.wide ? 8 : 4);
   const uint64_t DG = (uint64_t)b.dgp;
   const uint64_t ns = (uint64_t)std::max(s.n_stab, 1);
-  // small tables first priority; the permutation table joins them in LDS when
-  // both fit, otherwise it is read through the caches
+  // small tables first priority; the orbit search's tables take what they
+  // leave (up to the soft limit that keeps two workgroups on a CU), the rest
+  // of them is read through the caches
   uint64_t small = 0;
   small = align16(small + (uint64_t)s.G->order * (uint64_t)b.dgp * b.dgp * 8);
   small = align16(small + (uint64_t)std::max(s.n_stab, 1) * b.dgp * b.dgp * 8);
@@ -283,8 +282,14 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   small = align16(small + (uint64_t)s.nbonds * 8);
   small = align16(small + (uint64_t)(2 * s.d * s.d) * 8);
   small = align16(small + (uint64_t)s.nbonds * 2 * 4);
-  c.lds_tab = otf && align16(tab_bytes) + (small <= kSmallLdsBudget ? small : 0) <= kLdsLimit;
-  const uint32_t base = c.lds_tab ? align16(tab_bytes) : 0;
+  OrbitLds ol;
+  if (otf) {
+    const size_t room = kLdsLimit - 32 - (small <= kSmallLdsBudget ? small : 0);
+    ol = orbit_lds(s, room, room);
+  }
+  c.lds_tab = ol.tabs;
+  c.plain = s.plain() && s.gw <= 5 && ol.tabs;
+  const uint32_t base = align16(ol.bytes);
   uint64_t o = base;
   const uint32_t o_rho = (uint32_t)o;
   o = align16(o + (uint64_t)s.G->order * DG * DG * 8);
@@ -349,8 +354,14 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.fpar = b.fpar;
     a.zf = s.zflip ? 1 : 0;
     a.full = s.full;
+    a.mask = s.d_mask();
+    a.img = s.d_img();
+    a.split = s.d_split();
+    a.n_lds = ol.n_lds;
     a.nH = s.fac_nH;
     a.nT = s.fac_nT;
+    a.nch = s.nch;
+    a.NC = s.NC;
     a.n_stab = (int)ns;
     a.n_reps = s.n_reps;
     a.ld = ld;
@@ -365,15 +376,12 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.o_J = c.vg ? vg_J : o_J;
     a.o_fac = c.vg ? vg_fac : o_fac;
     a.o_bonds = c.vg ? vg_bonds : o_bonds;
-    a.tab = s.d_tab.p;
     a.cnt = s.d_cnt.p;
-    a.rank_bits = s.d_rank_bits.p;
-    a.rank_base = s.d_rank_base.p;
+    a.ranks = s.d_ranks.p;
     a.cnt_stride = s.cnt_stride;
     a.N = s.N;
     a.A_tot = s.A;
     a.D_M = s.D_M;
-    a.tab_words = (uint32_t)tab_words;
     a.scal = lz ? lz->scal : nullptr;
     a.partials = lz ? lz->partials : nullptr;
     a.eshift = lz ? lz->eshift : 0.0;

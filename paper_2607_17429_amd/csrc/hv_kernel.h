@@ -29,7 +29,10 @@
 //
 // Flips come from the sector's entry table (target index, h, flip id; built
 // once per sector and shared by all irreps) or are found on the fly (flip,
-// orbit search over the group, rank lookup).
+// orbit search over the group, rank lookup; the search's vector instructions
+// bound it: 4.6e5 representatives of the icosidodecahedron at 2M = 8, d = 4,
+// 7 FP32 vectors 1.63 ms, 9.15 ms with a walk over the group's images that
+// also searched for inadmissible flips).
 //
 // Lanczos epilogue (partials != nullptr): the kernel writes
 // w = s_j (H q_j) - bs_j q_prev over q_prev (Y holds q_prev on entry) and
@@ -84,50 +87,55 @@ struct HvArgs {
   const double* J;
   const double* fac;    // [2][dloc][dloc]
   int b, dloc, nbonds, G, n_stab;
-  int nH, nT;           // factored group G = T H of the on-the-fly search
   uint64_t n_reps;
   const T* X;
   T* Y;
   int64_t ld;
   int nvec, GL, log2GL, tile_w;
   int zero;  // always 0 (see the non-trivial stabilizer branch)
-  // dynamic LDS layout (byte offsets): [perm table][rho^T][V][stab][J][fac][bonds]
+  // dynamic LDS layout (byte offsets): [orbit search][rho^T][V][stab][J][fac][bonds]
   uint32_t o_rho, o_V, o_stab, o_J, o_fac, o_bonds;
-  // on-the-fly search
-  const void* tab;
+  // on-the-fly search (dev::Orbit; LDS: n_lds mask positions, counts, images)
+  const uint64_t* mask;
+  const void* img;
+  const uint32_t* split;
+  int n_lds, nH, nT, nch, NC;
   const uint64_t* cnt;
-  const uint64_t* rank_bits;
-  const uint32_t* rank_base;
+  const dev::RankWord* ranks;
   int cnt_stride, N, A_tot;
   int Gbase, zf;        // |G| and the spin flip of the on-the-fly search
   uint64_t full;
   double fpar;          // flip parity: element (g, F) acts as fpar * rho(g)
   uint64_t D_M;
-  uint32_t tab_words;
   // Lanczos epilogue
   const double* scal;
   double* partials;
   double eshift;        // H - eshift is applied (0 except for the Chebyshev recursion)
 };
 
+// On-the-fly kernels: NCH is 8 (32-bit labels) or 16, and NCH - 1 marks the
+// kernels of plain s = 1/2 sectors (dev::Orbit's PLAIN).
+template <int NCH, int GW>
+constexpr bool kPlain = GW > 0 && (NCH & 1);
+
 struct LaunchCfg {
   dim3 grid;
   size_t shm;
-  bool otf, lds_tab, slds, wide;
+  bool otf, lds_tab, slds, wide, plain;  // lds_tab: counts and images of the search in LDS
   bool contig;  // the dense gather holds: adjacent columns per lane
   bool vg;      // all small tables but V_S in LDS (table-driven H.V)
-  int nch, vpl;
+  int gw, vpl;
 };
 
 template <typename W>
 __device__ __forceinline__ bool lookup_rep(W r, int N, int b, int d, int A, const uint64_t* cnt, int stride,
-                                           uint64_t D_M, const uint64_t* bits, const uint32_t* base, uint64_t& idx) {
+                                           uint64_t D_M, const dev::RankWord* ranks, uint64_t& idx) {
   const uint64_t rk = dev::sector_rank<W>(r, N, b, d, A, cnt, stride);
   if (rk >= D_M) return false;
-  const uint64_t m = bits[rk >> 6];
+  const dev::RankWord w = ranks[rk >> 6];
   const int k = (int)(rk & 63);
-  idx = base[rk >> 6] + (uint64_t)__popcll(m & ((1ull << k) - 1));
-  return (m >> k) & 1;
+  idx = w.base + (uint64_t)__popcll(w.bits & ((1ull << k) - 1));
+  return (w.bits >> k) & 1;
 }
 
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
@@ -191,11 +199,15 @@ struct HvTabs {
 // The H.V over the representatives p = slot, slot + slot_stride, ... of one
 // column tile: lane group of GL lanes per representative (see the file text).
 // dot[j] accumulates q_j . w of this lane's column j in the Lanczos epilogue.
-template <typename T, int DG, int VPL, bool OTF, int NCH, bool CONTIG = false>
+// GW > 0: flips are found on the fly (orbit search with candidate sets of GW
+// words; osearch, ocnt: its tables); GW = 0: flips come from the entry table.
+template <typename T, int DG, int VPL, int GW, int NCH, bool CONTIG = false>
 __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
-                                        const dev::OrbitTabs<word_t<NCH>, NCH>& otabs, int tile, int ntiles,
+                                        const dev::Orbit<word_t<NCH>, (GW > 0 ? GW : 1), kPlain<NCH, GW>>& osearch,
+                                        const uint64_t* ocnt, int tile, int ntiles,
                                         uint64_t slot, uint64_t slot_stride, double (&dot)[VPL], bool (&vok)[VPL]) {
   using W = word_t<NCH>;
+  constexpr bool OTF = GW > 0;
   const bool EPI = a.partials != nullptr;
   const double* rhoT = tb.rhoT;
   const double* Vt = tb.Vt;
@@ -237,7 +249,38 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
       for (int j = 0; j < VPL; ++j) acc[q][j] = 0.0;
 
     const uint64_t e_begin = OTF ? 0 : a.row_ptr[p];
-    const uint64_t e_end = OTF ? (uint64_t)ncand : a.row_ptr[p + 1];
+    uint64_t e_end = OTF ? (uint64_t)ncand : a.row_ptr[p + 1];
+    // on the fly: the admissible flips of p as a bit mask where it fits 128
+    // bits, each lane of the group testing every GL-th one; e then counts
+    // admissible flips, so no lane searches for an inadmissible one
+    uint64_t adm0 = 0, adm1 = 0;
+    const bool listed = OTF && ncand <= 128;
+    if constexpr (OTF) {
+      if (listed) {
+        for (int q = lg; q < ncand; q += GL) {
+          const int bond = q >> 1;
+          const int ai = dev::digit(plab, bonds[2 * bond], a.b, lmask);
+          const int aj = dev::digit(plab, bonds[2 * bond + 1], a.b, lmask);
+          const uint64_t ok = (q & 1) ? (ai > 0 && aj < a.dloc - 1) : (ai < a.dloc - 1 && aj > 0);
+          if (q < 64)
+            adm0 |= ok << q;
+          else
+            adm1 |= ok << (q - 64);
+        }
+        for (int off = 1; off < GL; off <<= 1) {
+          adm0 |= shfl64(adm0, lane ^ off);
+          adm1 |= shfl64(adm1, lane ^ off);
+        }
+        e_end = (uint64_t)(__popcll(adm0) + __popcll(adm1));
+        // lane lg starts at the lg-th admissible flip
+        for (int q = 0; q < lg; ++q) {
+          if (adm0)
+            adm0 &= adm0 - 1;
+          else
+            adm1 &= adm1 - 1;
+        }
+      }
+    }
     for (uint64_t e = e_begin; e < e_end; e += GL) {
       // ---- one flip per lane: entry and target metadata
       uint64_t my = kInvalid;
@@ -252,10 +295,19 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
           }
         }
       } else {
-        const int cand = (int)e + lg;
-        bool ok = false;
+        int cand = (int)e + lg;
+        bool ok = cand < (int)e_end;
+        if (listed) {
+          cand = adm0 ? __builtin_ctzll(adm0) : adm1 ? 64 + __builtin_ctzll(adm1) : 0;
+          for (int q = 0; q < GL; ++q) {
+            if (adm0)
+              adm0 &= adm0 - 1;
+            else
+              adm1 &= adm1 - 1;
+          }
+        }
         W x = plab;
-        if (cand < ncand) {
+        if (ok) {
           const int bond = cand >> 1;
           const int i = bonds[2 * bond], j = bonds[2 * bond + 1];
           const int ai = dev::digit(plab, i, a.b, lmask), aj = dev::digit(plab, j, a.b, lmask);
@@ -264,11 +316,11 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
           if (ok) x = (cand & 1) ? (plab - ui + uj) : (plab + ui - uj);
         }
         W r;
-        int h;
-        dev::canon_min_z<W, NCH>(x, otabs, a.zf != 0, (W)a.full, a.Gbase, r, h);
+        int h, ties;
+        dev::orbit_min<W, GW, kPlain<NCH, GW>>(x, ok, osearch, r, h, ties);
         uint64_t idx = 0;
-        if (ok && lookup_rep<W>(r, a.N, a.b, a.dloc, a.A_tot, a.cnt, a.cnt_stride, a.D_M, a.rank_bits, a.rank_base, idx))
-          my = idx | ((uint64_t)h << 32) | ((uint64_t)cand << 48);
+        if (ok && lookup_rep<W>(r, a.N, a.b, a.dloc, a.A_tot, ocnt, a.cnt_stride, a.D_M, a.ranks, idx))
+          my = idx | ((uint64_t)h << 32) | ((uint64_t)cand << 48) | ((uint64_t)(ties == 1) << 63);
       }
       const uint32_t myidx = (uint32_t)(my & 0xffffffffu);
       uint64_t mm = 0;
@@ -451,7 +503,7 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
   }
 }
 
-template <typename T, int DG, int VPL, bool OTF, int NCH, bool LDS_TAB, bool SLDS, bool CONTIG = false,
+template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB, bool SLDS, bool CONTIG = false,
           bool VG = false>
 __global__ void __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(DG * VPL <= FTLM_HV_FLOOR_WIDTH ? FTLM_HV_WAVES_PER_EU : 1)))
@@ -460,9 +512,29 @@ k_hv(HvArgs<T> a) {
   extern __shared__ uint64_t smem_raw[];
   char* sm = (char*)smem_raw;
   const bool EPI = a.partials != nullptr;
-  const W* tab = nullptr;
-  if constexpr (OTF) tab = LDS_TAB ? stage<W>((const W*)a.tab, a.tab_words, sm) : (const W*)a.tab;
-  const dev::OrbitTabs<W, NCH> otabs = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
+  dev::Orbit<W, (GW > 0 ? GW : 1), kPlain<NCH, GW>> osearch{};
+  const uint64_t* ocnt = a.cnt;
+  if constexpr (GW > 0) {
+    const uint32_t pos = (uint32_t)(a.NC * 16 * GW), nc = (uint32_t)((a.N + 1) * a.cnt_stride);
+    osearch.mask = a.mask;
+    osearch.lds = stage<uint64_t>(a.mask, (uint32_t)a.n_lds * pos, sm);
+    osearch.n_lds = a.n_lds;
+    osearch.img = (const W*)a.img;
+    if constexpr (LDS_TAB) {
+      char* at = sm + (size_t)a.n_lds * pos * 8;
+      ocnt = stage<uint64_t>(a.cnt, nc, at);
+      osearch.img = stage<W>((const W*)a.img, (uint32_t)((a.nH + a.nT) * a.nch * 16), at + (size_t)nc * 8);
+    }
+    osearch.split = a.split;
+    osearch.nH = a.nH;
+    osearch.nch = a.nch;
+    osearch.NC = a.NC;
+    osearch.N = a.N;
+    osearch.b = a.b;
+    osearch.G = a.Gbase;
+    osearch.zf_ = a.zf != 0;
+    osearch.full = (W)a.full;
+  }
   const double* rhoT = a.rhoT;
   const double* Vt = a.V;
   const double* stabf = a.stabf;
@@ -477,7 +549,7 @@ k_hv(HvArgs<T> a) {
     fac = stage<double>(a.fac, (uint32_t)(2 * a.dloc * a.dloc), sm + a.o_fac);
     bonds = stage<int32_t>(a.bonds, (uint32_t)(2 * a.nbonds), sm + a.o_bonds);
   }
-  if constexpr (SLDS || (OTF && LDS_TAB)) __syncthreads();
+  if constexpr (SLDS || GW > 0) __syncthreads();
 
   const HvTabs tb{rhoT, Vt, stabf, Jb, fac, bonds};
   const int lane = threadIdx.x & 63;
@@ -488,7 +560,7 @@ k_hv(HvArgs<T> a) {
   const uint64_t slot_stride = (uint64_t)gridDim.x * waves * slots_per_wave;
   double dot[VPL];
   bool vok[VPL];
-  hv_pass<T, DG, VPL, OTF, NCH, CONTIG>(a, tb, otabs, (int)blockIdx.y, (int)gridDim.y, slot, slot_stride, dot, vok);
+  hv_pass<T, DG, VPL, GW, NCH, CONTIG>(a, tb, osearch, ocnt, (int)blockIdx.y, (int)gridDim.y, slot, slot_stride, dot, vok);
   if (EPI) {
     __shared__ double red[kThreads];
     // one vector slot j at a time: lanes with equal lg hold the same column
@@ -507,29 +579,29 @@ k_hv(HvArgs<T> a) {
   }
 }
 
-template <typename T, int DG, int VPL, bool OTF, int NCH, bool LDS_TAB>
+template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB>
 void launch_k(const HvArgs<T>& a, const LaunchCfg& c, hipStream_t st) {
   // adjacent-column kernels for the dimension buckets 1-6 (a dense launch of
   // bucket 8 or 12 needs d_Gamma exactly 8 or 12; it takes the default layout)
-  if constexpr (!OTF && DG <= 6) {
+  if constexpr (GW == 0 && DG <= 6) {
     if (c.slds && c.contig) {
       if (c.vg)
-        hipLaunchKernelGGL((k_hv<T, DG, VPL, OTF, NCH, LDS_TAB, true, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
+        hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
       else
-        hipLaunchKernelGGL((k_hv<T, DG, VPL, OTF, NCH, LDS_TAB, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
+        hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
       return;
     }
   }
-  if constexpr (!OTF) {
+  if constexpr (GW == 0) {
     if (c.slds && c.vg) {
-      hipLaunchKernelGGL((k_hv<T, DG, VPL, OTF, NCH, LDS_TAB, true, false, true>), c.grid, dim3(kThreads), c.shm, st, a);
+      hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, false, true>), c.grid, dim3(kThreads), c.shm, st, a);
       return;
     }
   }
   if (c.slds)
-    hipLaunchKernelGGL((k_hv<T, DG, VPL, OTF, NCH, LDS_TAB, true>), c.grid, dim3(kThreads), c.shm, st, a);
-  else if constexpr (!OTF)
-    hipLaunchKernelGGL((k_hv<T, DG, VPL, OTF, NCH, LDS_TAB, false>), c.grid, dim3(kThreads), c.shm, st, a);
+    hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true>), c.grid, dim3(kThreads), c.shm, st, a);
+  else if constexpr (GW == 0)
+    hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, false>), c.grid, dim3(kThreads), c.shm, st, a);
   else
     fail(FTLM_ERR_UNSUPPORTED, "on-the-fly H.V needs the irrep tables in LDS");
 }
@@ -539,17 +611,22 @@ void launch_vpl(const HvArgs<T>& a, const LaunchCfg& c, hipStream_t st) {
   if (!c.otf) {
     // the label word width still matters: flips read p's digits
     if (c.wide)
-      launch_k<T, DG, VPL, false, 16, false>(a, c, st);
+      launch_k<T, DG, VPL, 0, 16, false>(a, c, st);
     else
-      launch_k<T, DG, VPL, false, 8, false>(a, c, st);
+      launch_k<T, DG, VPL, 0, 8, false>(a, c, st);
     return;
   }
   if constexpr (VPL == 1 || VPL == 4) {
-    FTLM_DISPATCH_NCH(c.nch, {
-      if (c.lds_tab)
-        launch_k<T, DG, VPL, true, NCH, true>(a, c, st);
-      else
-        launch_k<T, DG, VPL, true, NCH, false>(a, c, st);
+    FTLM_DISPATCH_ORBIT(c.wide, c.plain, c.gw, {
+      constexpr int NCH = (sizeof(W) == 4 ? 8 : 16) - (PLAIN ? 1 : 0);
+      // plain kernels only for groups of up to 320 elements with every search
+      // table in LDS (c.plain); everything else takes the general ones
+      if constexpr (!PLAIN || GW <= 5) {
+        if (PLAIN || c.lds_tab)
+          launch_k<T, DG, VPL, GW, NCH, true>(a, c, st);
+        else if constexpr (!PLAIN)
+          launch_k<T, DG, VPL, GW, NCH, false>(a, c, st);
+      }
     });
   } else {
     fail(FTLM_ERR_INVALID_ARG, "on-the-fly H.V uses 1 or 4 vectors per lane");

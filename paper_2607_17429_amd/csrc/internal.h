@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "device.h"
 #include "group.h"
 
 struct ftlm_group {
@@ -27,7 +28,9 @@ struct Sector {
   int nbonds = 0;
   bool wide = false;            // labels need 64 bits (N * bits > 32)
   int nch = 0;                  // 4-bit chunks of a packed label
+  int gw = 2;                   // 64-bit words of a candidate set (orbit_words)
   bool zflip = false;           // M = 0 resolved by G x Z2 (global spin flip)
+  bool plain() const { return bits == 1 && !zflip; }  // dev::Orbit's PLAIN
   uint64_t full = 0;            // packed label with every digit d - 1
   int gorder = 0;               // |G|, or 2|G| with the spin flip (element (g, f) = f|G| + g)
   uint64_t D_M = 0, n_reps = 0, n_words = 0;
@@ -41,14 +44,16 @@ struct Sector {
   std::vector<std::vector<int32_t>> stab_elems;  // per stabilizer id
   int32_t n_stab = 0;
   // device tables
-  // chunk tables of the factored group G = T H: (|H| + |T|) x nch x 16 words
-  // (uint32 or uint64 payload), then |T| x |H| uint16 element indices
+  // orbit search (dev::Orbit): N x NC x 16 x gw mask words, the image tables of
+  // the factored group G = T H ((|H| + |T|) x nch x 16 label words), split[|G|]
   DevBuf<uint64_t> d_tab;
-  int fac_nH = 1, fac_nT = 1;
-  uint32_t tab_words = 0;       // in payload words
+  int fac_nH = 1, fac_nT = 1, NC = 1;
+  size_t mask_words = 0, img_bytes = 0;
+  const uint64_t* d_mask() const { return d_tab.p; }
+  const void* d_img() const { return d_tab.p + mask_words; }
+  const uint32_t* d_split() const { return (const uint32_t*)((const uint8_t*)d_tab.p + mask_words * 8 + img_bytes); }
   DevBuf<uint64_t> d_cnt;
-  DevBuf<uint64_t> d_rank_bits; // bitmap over sector ranks
-  DevBuf<uint32_t> d_rank_base; // representatives before each word
+  DevBuf<dev::RankWord> d_ranks; // bitmap over sector ranks, representatives before each word
   DevBuf<uint64_t> d_reps;      // packed labels, ascending
   DevBuf<uint16_t> d_stab_id;
   DevBuf<double> d_ediag;       // Eq. (16) per representative
@@ -67,7 +72,7 @@ struct Sector {
   DevBuf<double> d_J;
   DevBuf<double> d_fac;         // [2][d][d] ladder products (J = 1)
   int64_t device_bytes() const {
-    return (int64_t)(d_tab.bytes() + d_cnt.bytes() + d_rank_bits.bytes() + d_rank_base.bytes() +
+    return (int64_t)(d_tab.bytes() + d_cnt.bytes() + d_ranks.bytes() +
                      d_reps.bytes() + d_stab_id.bytes() + d_ediag.bytes() + d_row_ptr.bytes() +
                      d_entries.bytes() + d_eidx.bytes() + d_ehc.bytes() + d_bonds.bytes() + d_J.bytes() +
                      d_fac.bytes());
@@ -106,6 +111,15 @@ void sector_canonicalize(const Sector& s, const uint64_t* labels, int64_t n, uin
                          int64_t* index, hipStream_t stream);
 std::vector<uint64_t> sector_export_labels(const Sector& s);
 
+// LDS of an orbit-search kernel: mask positions and, with tabs, the digit-sum
+// counts and image tables (bytes in all), within `limit` bytes.
+struct OrbitLds {
+  int n_lds = 0;
+  bool tabs = false;
+  size_t bytes = 0;
+};
+OrbitLds orbit_lds(const Sector& s, size_t soft, size_t limit);
+
 std::unique_ptr<Block> build_block(std::shared_ptr<Sector> sec, int irrep, int row, const ftlm_opts* opts);
 void block_hv_stats(const Block& b, ftlm_hv_stats* st);
 
@@ -139,9 +153,6 @@ VecLayout vec_layout(const Block& b, int kind, int64_t row_bytes);
 // the layout ftlm_run and ftlm_kpm take for this block and row size
 VecLayout run_layout(const Block& b, int64_t row_bytes);
 uint64_t vec_rows(const Block& b, const VecLayout& v);
-namespace dev {
-struct PadMap;
-}
 // the device row map of a padded layout
 dev::PadMap pad_map(const Block& b, const VecLayout& v);
 

@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* _
                   stage<double>(a.J, (uint32_t)a.nbonds, sm + a.o_J),
                   stage<double>(a.fac, (uint32_t)(2 * a.dloc * a.dloc), sm + a.o_fac),
                   stage<int32_t>(a.bonds, (uint32_t)(2 * a.nbonds), sm + a.o_bonds)};
-  const dev::OrbitTabs<W, NCH> otabs = dev::orbit_tabs<W, NCH>((const W*)nullptr, 1, 1);  // entries: unused
+  const dev::Orbit<W, 1, false> none{};  // flips come from the entry table
   for (int i = t; i < R * steps; i += NT) {
     alpha[i] = 0.0;
     beta[i] = 0.0;
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* _
     a.Y = qp;
     double dot[VPL];
     bool vok[VPL];
-    hv_pass<T, DG, VPL, false, NCH>(a, tb, otabs, 0, 1, slot, slot_stride, dot, vok);
+    hv_pass<T, DG, VPL, 0, NCH>(a, tb, none, nullptr, 0, 1, slot, slot_stride, dot, vok);
     // column sums of q_j . w: lanes with equal (lane mod GL) hold the same column
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {

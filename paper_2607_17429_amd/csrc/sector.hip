@@ -25,70 +25,106 @@ namespace ftlm {
 namespace {
 
 constexpr int kThreads = 256;
-
-template <typename W, bool LDS>
-__device__ __forceinline__ const W* stage_table(const W* g_tab, uint32_t n_words, W* smem) {
-  if constexpr (!LDS) {
-    return g_tab;
-  } else {
-    for (uint32_t i = threadIdx.x; i < n_words; i += blockDim.x) smem[i] = g_tab[i];
-    __syncthreads();
-    return smem;
-  }
-}
+// threads of the orbit-search kernels: their LDS tables (up to about 50 KiB)
+// are shared by 8 waves, three workgroups to a CU
+constexpr int kOrbitThreads = 512;
 
 struct SecArgs {
-  const void* tab;   // factored chunk tables (dev::OrbitTabs layout)
+  // orbit search (dev::Orbit): masks, image tables, element splits
+  const uint64_t* mask;
+  const void* img;
+  const uint32_t* split;
+  int n_lds, nH, nT, nch, NC;
   const uint64_t* cnt;
   int cnt_stride;
-  int N, b, d, A, G, nH, nT;
+  int N, b, d, A, G;
   int zf;          // resolve by the spin flip too (G x Z2)
   uint64_t full;   // packed label with every digit d - 1 (F x = full - x)
   uint64_t D_M, n_words, n_reps;
-  uint32_t tab_words;
+  int transitive;  // the group moves every site to every other
 };
 
+template <typename E>
+__device__ __forceinline__ void stage_copy(E* dst, const E* src, size_t n) {
+  for (size_t i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
+}
+
+// The orbit-search tables of a kernel: the first n_lds mask positions in LDS,
+// and with TABS the digit-sum counts and the image tables as well.
+template <typename W, int GW, bool PLAIN, bool TABS>
+__device__ __forceinline__ dev::Orbit<W, GW, PLAIN> stage_orbit(const SecArgs& a, uint64_t* smem, const uint64_t*& cnt) {
+  const size_t pos = (size_t)a.NC * 16 * GW;
+  stage_copy(smem, a.mask, (size_t)a.n_lds * pos);
+  dev::Orbit<W, GW, PLAIN> o;
+  o.mask = a.mask;
+  o.lds = smem;
+  o.n_lds = a.n_lds;
+  o.split = a.split;
+  o.nH = a.nH;
+  o.nch = a.nch;
+  o.NC = a.NC;
+  o.N = a.N;
+  o.b = a.b;
+  o.G = a.G;
+  o.zf_ = a.zf != 0;
+  o.full = (W)a.full;
+  if constexpr (TABS) {
+    uint64_t* c = smem + (size_t)a.n_lds * pos;
+    const size_t nc = (size_t)(a.N + 1) * a.cnt_stride;
+    stage_copy(c, a.cnt, nc);
+    W* t = (W*)(c + nc);
+    stage_copy(t, (const W*)a.img, (size_t)(a.nH + a.nT) * a.nch * 16);
+    cnt = c;
+    o.img = t;
+  } else {
+    cnt = a.cnt;
+    o.img = (const W*)a.img;
+  }
+  __syncthreads();
+  return o;
+}
+
 // ---- representative sweep --------------------------------------------------
-template <typename W, int NCH, bool LDS>
-__global__ void __launch_bounds__(kThreads) k_enum(SecArgs a, uint64_t* __restrict__ bits_out) {
+// Word w of the bitmap covers ranks [64 w, 64 w + 64).  WAVE = false: one
+// thread per word unranks its first label and steps through the others in
+// label order, 64 consecutive words per wave, so the lanes' labels share
+// their high bits and mostly fail at the same position.  WAVE = true, for
+// sectors of too few words to fill the device that way: one wave per word,
+// every lane unranks its own label and the vote is the word.
+// Bound by vector instructions (about 200 per label and wave, 61% busy) and
+// branches.  1.55e8 labels of the s = 1/2 icosidodecahedron at M = 0: 1.19 ms
+// against 1.53 ms with the images of all elements; the 924 labels of the
+// icosahedron: 13 us (one wave per word) against 201 us.
+template <typename W, int GW, bool PLAIN, bool TABS, bool WAVE>
+__global__ void __launch_bounds__(kOrbitThreads) k_enum(SecArgs a, uint64_t* __restrict__ bits_out) {
   extern __shared__ uint64_t smem_raw[];
-  const W* tab = stage_table<W, LDS>((const W*)a.tab, a.tab_words, (W*)smem_raw);
+  const uint64_t* cnt;
+  const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
+  const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  const dev::OrbitTabs<W, NCH> o = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
-  for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < a.n_words; w += stride) {
-    W x = dev::sector_unrank<W>(w * 64, a.N, a.b, a.d, a.A, a.cnt, a.cnt_stride);
-    uint64_t bits = 0;
-    for (int k = 0; k < 64; ++k) {
-      const bool valid = w * 64 + k < a.D_M;
-      int offx[NCH];
-      dev::chunk_offsets<W, NCH>(x, offx);
-      const W fx = (W)a.full - x;
-      bool smaller = a.zf && fx < x;  // (e, F)
-      // walk g = t h; every lane runs the same trip counts, so the vote is uniform
-      int step = 0;
-      for (int hi = 0; hi < o.nH; ++hi) {
-        int off[NCH];
-        if (hi == 0) {
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) off[c] = offx[c];
-        } else {
-          dev::chunk_offsets<W, NCH>(dev::permute<W, NCH>(o.H, hi, offx), off);
-        }
-        bool done = false;
-        for (int ti = hi == 0 ? 1 : 0; ti < o.nT; ++ti) {
-          const W img = dev::permute<W, NCH>(o.T, ti, off);
-          smaller |= img < x || (a.zf && img > fx);  // F(img) < x
-          if ((++step & 3) == 0 && __all(smaller || !valid)) {
-            done = true;
-            break;
-          }
-        }
-        if (done) break;
-      }
-      if (valid && !smaller) bits |= 1ull << k;
-      x = dev::sector_next<W>(x, a.N, a.b, a.d);
+  if constexpr (WAVE) {
+    for (uint64_t w = t0 >> 6; w < a.n_words; w += stride >> 6) {
+      const uint64_t rank = w * 64 + (threadIdx.x & 63);
+      const bool live = rank < a.D_M;
+      const W x = dev::sector_unrank<W>(live ? rank : 0, a.N, a.b, a.d, a.A, cnt, a.cnt_stride);
+      const uint64_t bits = __ballot(dev::is_orbit_min<W, GW, PLAIN>(x, live, o));
+      if ((threadIdx.x & 63) == 0) bits_out[w] = bits;
     }
-    bits_out[w] = bits;
+  } else {
+    for (uint64_t w = t0; w < a.n_words; w += stride) {
+      W x = dev::sector_unrank<W>(w * 64, a.N, a.b, a.d, a.A, cnt, a.cnt_stride);
+      uint64_t bits = 0;
+      // the top digit only grows along the word, and a transitive group can
+      // bring any digit to the top: above the mean digit no label is minimal
+      // (for d = 2 every label with the top bit set, half of them at M = 0)
+      const int top = (int)(x >> ((a.N - 1) * a.b));
+      for (int k = 0; k < 64 && !(a.transitive && a.A < a.N * top); ++k) {
+        const bool live = w * 64 + k < a.D_M;
+        if (dev::is_orbit_min<W, GW, PLAIN>(x, live, o)) bits |= 1ull << k;
+        x = dev::sector_next<W>(x, a.N, a.b, a.d);
+      }
+      bits_out[w] = bits;
+    }
   }
 }
 
@@ -97,20 +133,21 @@ __global__ void k_popcount(const uint64_t* __restrict__ bits, uint64_t* __restri
     out[i] = __popcll(bits[i]);
 }
 
-__global__ void k_to_u32(const uint64_t* __restrict__ in, uint32_t* __restrict__ out, uint64_t n) {
+__global__ void k_rank_words(const uint64_t* __restrict__ bits, const uint64_t* __restrict__ base,
+                             dev::RankWord* __restrict__ out, uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    out[i] = (uint32_t)in[i];
+    out[i] = dev::RankWord{bits[i], (uint32_t)base[i], 0u};
 }
 
 template <typename W>
-__global__ void __launch_bounds__(kThreads) k_extract(SecArgs a, const uint64_t* __restrict__ bits,
-                                                     const uint32_t* __restrict__ base, uint64_t* __restrict__ reps) {
+__global__ void __launch_bounds__(kThreads) k_extract(SecArgs a, const dev::RankWord* __restrict__ ranks,
+                                                     uint64_t* __restrict__ reps) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < a.n_words; w += stride) {
-    uint64_t m = bits[w];
+    const uint64_t m = ranks[w].bits;
     if (!m) continue;
     W x = dev::sector_unrank<W>(w * 64, a.N, a.b, a.d, a.A, a.cnt, a.cnt_stride);
-    uint64_t j = base[w];
+    uint64_t j = ranks[w].base;
     const int top = 63 - __clzll(m);
     for (int k = 0; k <= top; ++k) {
       if ((m >> k) & 1) reps[j++] = (uint64_t)x;
@@ -120,75 +157,49 @@ __global__ void __launch_bounds__(kThreads) k_extract(SecArgs a, const uint64_t*
 }
 
 // ---- stabilizers -----------------------------------------------------------
-// flag[i] = 1 when some g != e fixes representative i.
-template <typename W, int NCH, bool LDS>
-__global__ void __launch_bounds__(kThreads) k_stab_flag(SecArgs a, const uint64_t* __restrict__ reps,
-                                                       uint64_t* __restrict__ flag) {
+// flag[i] = 1 when some element other than e fixes representative i.
+template <typename W, int GW, bool PLAIN, bool TABS>
+__global__ void __launch_bounds__(kOrbitThreads) k_stab_flag(SecArgs a, const uint64_t* __restrict__ reps,
+                                                            uint64_t* __restrict__ flag) {
   extern __shared__ uint64_t smem_raw[];
-  const W* tab = stage_table<W, LDS>((const W*)a.tab, a.tab_words, (W*)smem_raw);
-  const dev::OrbitTabs<W, NCH> o = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
+  const uint64_t* cnt;
+  const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_reps; i += stride) {
-    const W r = (W)reps[i];
-    int offr[NCH];
-    dev::chunk_offsets<W, NCH>(r, offr);
-    const W fr = (W)a.full - r;
-    bool fixed = a.zf && fr == r;  // (e, F)
-    int step = 0;
-    for (int hi = 0; hi < o.nH; ++hi) {
-      int off[NCH];
-      if (hi == 0) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) off[c] = offr[c];
-      } else {
-        dev::chunk_offsets<W, NCH>(dev::permute<W, NCH>(o.H, hi, offr), off);
-      }
-      bool done = false;
-      for (int ti = hi == 0 ? 1 : 0; ti < o.nT; ++ti) {
-        const W img = dev::permute<W, NCH>(o.T, ti, off);
-        fixed |= img == r || (a.zf && img == fr);
-        if ((++step & 3) == 0 && __all(fixed)) {
-          done = true;
-          break;
-        }
-      }
-      if (done) break;
-    }
-    flag[i] = fixed ? 1 : 0;
+    uint64_t lo[GW], hi[GW];
+    dev::stabilizer<W, GW, PLAIN>((W)reps[i], true, o, lo, hi);
+    flag[i] = dev::count<GW>(lo) + dev::count<GW>(hi) > 1 ? 1 : 0;
   }
 }
 
 // Full stabilizer masks of the representatives with a non-trivial stabilizer,
 // written compacted (pos = exclusive scan of the flags, pos[n_reps] = count).
-template <typename W, int NCH, bool LDS>
-__global__ void __launch_bounds__(kThreads) k_stab_mask(SecArgs a, const uint64_t* __restrict__ reps,
-                                                       const uint64_t* __restrict__ pos, int mw,
-                                                       uint64_t* __restrict__ masks, uint64_t* __restrict__ idx_out) {
+template <typename W, int GW, bool PLAIN, bool TABS>
+__global__ void __launch_bounds__(kOrbitThreads) k_stab_mask(SecArgs a, const uint64_t* __restrict__ reps,
+                                                            const uint64_t* __restrict__ pos, int mw,
+                                                            uint64_t* __restrict__ masks,
+                                                            uint64_t* __restrict__ idx_out) {
   extern __shared__ uint64_t smem_raw[];
-  const W* tab = stage_table<W, LDS>((const W*)a.tab, a.tab_words, (W*)smem_raw);
-  const dev::OrbitTabs<W, NCH> o = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
+  const uint64_t* cnt;
+  const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_reps; i += stride) {
     const uint64_t p = pos[i];
     if (pos[i + 1] == p) continue;
-    const W r = (W)reps[i];
-    const W fr = (W)a.full - r;
-    int offr[NCH];
-    dev::chunk_offsets<W, NCH>(r, offr);
+    uint64_t lo[GW], hi[GW];
+    dev::stabilizer<W, GW, PLAIN>((W)reps[i], true, o, lo, hi);
+    // element (g, F) is bit |G| + g of the mask
     uint64_t* mk = masks + p * mw;
-    for (int wq = 0; wq < mw; ++wq) mk[wq] = 0;
-    for (int hi = 0; hi < o.nH; ++hi) {
-      int off[NCH];
-      dev::chunk_offsets<W, NCH>(dev::permute<W, NCH>(o.H, hi, offr), off);
-      for (int ti = 0; ti < o.nT; ++ti) {
-        const W img = dev::permute<W, NCH>(o.T, ti, off);
-        const int g = o.gidx[ti * o.nH + hi];
-        if (img == r) mk[g >> 6] |= 1ull << (g & 63);   // this lane's own mask words
-        if (a.zf && img == fr) {
-          const int gf = a.G + g;                       // (g, F)
-          mk[gf >> 6] |= 1ull << (gf & 63);
-        }
+    for (int wq = 0; wq < mw; ++wq) {
+      uint64_t m = 0;
+#pragma unroll
+      for (int q = 0; q < GW; ++q) {
+        if (q == wq) m |= lo[q];
+        const int at = a.G + 64 * q - 64 * wq;  // where hi's word q starts in this word
+        if (at >= 0 && at < 64) m |= hi[q] << at;
+        if (at < 0 && at > -64) m |= hi[q] >> -at;
       }
+      mk[wq] = m;
     }
     idx_out[p] = i;
   }
@@ -244,106 +255,138 @@ __device__ __forceinline__ W apply_flip(W p, int cand, const FlipArgs& f, int b)
 }
 
 template <typename W>
-__device__ __forceinline__ int next_admissible(W p, int cur, int ncand, const FlipArgs& f, int b, int d, W mask) {
-  for (int c = cur + 1; c < ncand; ++c)
-    if (admissible(p, c, f, b, d, mask)) return c;
-  return -1;
-}
-
-template <typename W>
 __global__ void __launch_bounds__(kThreads) k_entry_count(SecArgs a, FlipArgs f, const uint64_t* __restrict__ reps,
                                                          uint64_t* __restrict__ counts, double* __restrict__ ediag) {
   const W mask = (W(1) << a.b) - 1;
   const double s = 0.5 * (a.d - 1);
-  const int ncand = 2 * f.nbonds;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_reps; i += stride) {
     const W p = (W)reps[i];
     uint64_t c = 0;
-    for (int q = 0; q < ncand; ++q) c += admissible(p, q, f, a.b, a.d, mask) ? 1 : 0;
-    counts[i] = c;
     double e = 0;
     for (int bnd = 0; bnd < f.nbonds; ++bnd) {
-      const double mi = dev::digit(p, f.bonds[2 * bnd], a.b, mask) - s;
-      const double mj = dev::digit(p, f.bonds[2 * bnd + 1], a.b, mask) - s;
-      e += f.J[bnd] * mi * mj;
+      const int ai = dev::digit(p, f.bonds[2 * bnd], a.b, mask), aj = dev::digit(p, f.bonds[2 * bnd + 1], a.b, mask);
+      c += (ai < a.d - 1 && aj > 0) + (ai > 0 && aj < a.d - 1);
+      e += f.J[bnd] * (ai - s) * (aj - s);
     }
+    counts[i] = c;
     ediag[i] = e;
   }
 }
 
 template <typename W>
-__device__ __forceinline__ bool lookup(W r, const SecArgs& a, const uint64_t* __restrict__ bits,
-                                       const uint32_t* __restrict__ base, uint64_t& idx) {
-  const uint64_t rk = dev::sector_rank<W>(r, a.N, a.b, a.d, a.A, a.cnt, a.cnt_stride);
+__device__ __forceinline__ bool lookup(W r, const SecArgs& a, const dev::RankWord* __restrict__ ranks,
+                                       const uint64_t* cnt, uint64_t& idx) {
+  const uint64_t rk = dev::sector_rank<W>(r, a.N, a.b, a.d, a.A, cnt, a.cnt_stride);
   if (rk >= a.D_M) return false;
-  const uint64_t w = rk >> 6;
-  const uint64_t m = bits[w];
+  const dev::RankWord w = ranks[rk >> 6];
   const int k = (int)(rk & 63);
-  idx = base[w] + (uint64_t)__popcll(m & ((1ull << k) - 1));
-  return (m >> k) & 1;
+  idx = w.base + (uint64_t)__popcll(w.bits & ((1ull << k) - 1));
+  return (w.bits >> k) & 1;
 }
 
-// One lane per representative; in round t every lane canonicalizes its t-th
-// admissible flip, so all lanes walk the group elements together.
-template <typename W, int NCH, bool LDS>
-__global__ void __launch_bounds__(kThreads) k_entry_fill(SecArgs a, FlipArgs f, const uint64_t* __restrict__ reps,
-                                                        const uint64_t* __restrict__ row_ptr,
-                                                        const uint64_t* __restrict__ bits,
-                                                        const uint32_t* __restrict__ base,
-                                                        uint64_t* __restrict__ entries,
-                                                        uint32_t* __restrict__ eidx, uint16_t* __restrict__ ehc,
-                                                        int hbits, const uint16_t* __restrict__ stab_id,
-                                                        uint16_t triv_sid) {
+// The entries of a workgroup's representatives (group i0 = blockIdx.x * rb,
+// rb at most kFillReps, and so on by the grid): their admissible flips are
+// listed in LDS in entry order, then one lane takes one flip, so every lane
+// of the orbit search has work and neighbouring lanes write neighbouring
+// entries (a lane per representative left the lanes of short rows idle and
+// gave a sector of a few representatives to a few lanes, one flip after the
+// other).  Bound by vector instructions (78% busy; the lookup is one random
+// 16-byte read).  4.02e7 flips of the s = 1/2 icosidodecahedron at M = 0:
+// 2.17 ms against 4.51 ms; the icosahedron's sectors 17 us against 257 us.
+constexpr int kFillReps = 64;
+constexpr int kFillList = 4096;  // listed flips per pass (16 KiB)
+
+template <typename W, int GW, bool PLAIN, bool TABS>
+__global__ void __launch_bounds__(kOrbitThreads) k_entry_fill(SecArgs a, FlipArgs f, int rb, const uint64_t* __restrict__ reps,
+                                                             const uint64_t* __restrict__ row_ptr,
+                                                             const dev::RankWord* __restrict__ ranks,
+                                                             uint64_t* __restrict__ entries,
+                                                             uint32_t* __restrict__ eidx, uint16_t* __restrict__ ehc,
+                                                             int hbits) {
   extern __shared__ uint64_t smem_raw[];
-  const W* tab = stage_table<W, LDS>((const W*)a.tab, a.tab_words, (W*)smem_raw);
-  const dev::OrbitTabs<W, NCH> o = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
+  __shared__ uint32_t list[kFillList];       // representative in the group << 16 | flip
+  __shared__ uint32_t from[kFillReps + 1];   // first listed flip of each representative
+  __shared__ uint64_t done[kFillReps];       // entries written before this pass
+  const uint64_t* cnt;
+  const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
   const W mask = (W(1) << a.b) - 1;
   const int ncand = 2 * f.nbonds;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  const uint64_t n_iter = (a.n_reps + stride - 1) / stride;  // same trip count on every lane
-  for (uint64_t it = 0; it < n_iter; ++it) {
-    const uint64_t i = it * stride + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = i < a.n_reps;
-    const W p = live ? (W)reps[i] : W(0);
-    uint64_t out = live ? row_ptr[i] : 0;
-    int cur = live ? next_admissible<W>(p, -1, ncand, f, a.b, a.d, mask) : -1;
-    while (__any(cur >= 0)) {
-      const W x = cur >= 0 ? apply_flip<W>(p, cur, f, a.b) : p;
-      W r;
-      int h;
-      dev::canon_min_z<W, NCH>(x, o, a.zf, (W)a.full, a.G, r, h);
-      if (cur >= 0) {
-        uint64_t idx = 0;
-        bool ok = lookup<W>(r, a, bits, base, idx);
-        // a canonical label of the sector is always a representative
-        // top bit: the target's stabilizer is trivial (its n_Gamma, L and V
-        // are then known without reading its stabilizer id)
-        const bool triv = ok && stab_id[idx] == triv_sid;
-        if (eidx) {
-          eidx[out] = ok ? (uint32_t)idx : 0xFFFFFFFFu;
-          ehc[out] = (uint16_t)(h | (cur << hbits) | (triv ? 0x8000 : 0));
-          ++out;
-        } else {
-          entries[out++] = (ok ? idx : 0xFFFFFFFFull) | ((uint64_t)h << 32) | ((uint64_t)cur << 48) |
-                           (triv ? (1ull << 63) : 0ull);
-        }
-        cur = next_admissible<W>(p, cur, ncand, f, a.b, a.d, mask);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int span = min(ncand, kFillList / rb);  // flips of one representative per pass
+  for (uint64_t i0 = (uint64_t)blockIdx.x * rb; i0 < a.n_reps; i0 += (uint64_t)gridDim.x * rb) {
+    const int n = (int)min((uint64_t)rb, a.n_reps - i0);
+    for (int r = threadIdx.x; r < n; r += blockDim.x) done[r] = row_ptr[i0 + r];
+    for (int q0 = 0; q0 < ncand; q0 += span) {
+      const int q1 = min(q0 + span, ncand);
+      __syncthreads();  // the last pass is through with list, from and done
+      // count, offsets, list: one wave per representative
+      for (int r = wave; r < n; r += waves) {
+        const W p = (W)reps[i0 + r];
+        uint32_t c = 0;
+        for (int q = q0 + lane; __any(q < q1); q += 64)
+          c += __popcll(__ballot(q < q1 && admissible(p, q, f, a.b, a.d, mask)));
+        if (lane == 0) from[r + 1] = c;
       }
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        from[0] = 0;
+        for (int r = 0; r < n; ++r) from[r + 1] += from[r];
+      }
+      __syncthreads();
+      for (int r = wave; r < n; r += waves) {
+        const W p = (W)reps[i0 + r];
+        uint32_t at = from[r];
+        for (int q = q0 + lane; __any(q < q1); q += 64) {
+          const bool ok = q < q1 && admissible(p, q, f, a.b, a.d, mask);
+          const uint64_t m = __ballot(ok);
+          if (ok) list[at + __popcll(m & ((1ull << lane) - 1))] = ((uint32_t)r << 16) | (uint32_t)q;
+          at += __popcll(m);
+        }
+      }
+      __syncthreads();
+      const uint32_t total = from[n];
+      for (uint32_t e0 = 0; e0 < total; e0 += blockDim.x) {
+        const uint32_t e = e0 + threadIdx.x;
+        const bool live = e < total;
+        const uint32_t rq = list[live ? e : 0];
+        const int r = (int)(rq >> 16), cur = (int)(rq & 0xffffu);
+        W t;
+        int h, ties;
+        dev::orbit_min<W, GW, PLAIN>(apply_flip<W>((W)reps[i0 + r], cur, f, a.b), live, o, t, h, ties);
+        if (live) {
+          uint64_t idx = 0;
+          const bool ok = lookup<W>(t, a, ranks, cnt, idx);
+          // a canonical label of the sector is always a representative
+          // top bit: the target's stabilizer is trivial, one element reaches it
+          // (its n_Gamma, L and V are then known without its stabilizer id)
+          const bool triv = ok && ties == 1;
+          const uint64_t out = done[r] + (e - from[r]);
+          if (eidx) {
+            eidx[out] = ok ? (uint32_t)idx : 0xFFFFFFFFu;
+            ehc[out] = (uint16_t)(h | (cur << hbits) | (triv ? 0x8000 : 0));
+          } else {
+            entries[out] = (ok ? idx : 0xFFFFFFFFull) | ((uint64_t)h << 32) | ((uint64_t)cur << 48) |
+                           (triv ? (1ull << 63) : 0ull);
+          }
+        }
+      }
+      __syncthreads();
+      for (int r = threadIdx.x; r < n; r += blockDim.x) done[r] += from[r + 1] - from[r];
     }
+    __syncthreads();
   }
 }
 
 // ---- orbit search for arbitrary labels (test / export entry point) ---------
-template <typename W, int NCH, bool LDS>
-__global__ void __launch_bounds__(kThreads) k_canon_labels(SecArgs a, const uint64_t* __restrict__ bits,
-                                                          const uint32_t* __restrict__ base,
+template <typename W, int GW, bool PLAIN, bool TABS>
+__global__ void __launch_bounds__(kOrbitThreads) k_canon_labels(SecArgs a, const dev::RankWord* __restrict__ ranks,
                                                           const uint64_t* __restrict__ labels, int64_t n,
                                                           uint64_t* __restrict__ rep_out, int32_t* __restrict__ h_out,
                                                           int64_t* __restrict__ idx_out) {
   extern __shared__ uint64_t smem_raw[];
-  const W* tab = stage_table<W, LDS>((const W*)a.tab, a.tab_words, (W*)smem_raw);
-  const dev::OrbitTabs<W, NCH> o = dev::orbit_tabs<W, NCH>(tab, a.nH, a.nT);
+  const uint64_t* cnt;
+  const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t n_iter = (n + stride - 1) / stride;
   for (int64_t it = 0; it < n_iter; ++it) {
@@ -365,11 +408,11 @@ __global__ void __launch_bounds__(kThreads) k_canon_labels(SecArgs a, const uint
       in_range = (y == 0) && (sum == a.A);
     }
     W r;
-    int h;
-    dev::canon_min_z<W, NCH>(x, o, a.zf, (W)a.full, a.G, r, h);
+    int h, ties;
+    dev::orbit_min<W, GW, PLAIN>(x, live, o, r, h, ties);
     if (live) {
       uint64_t idx = 0;
-      bool ok = in_range && lookup<W>(r, a, bits, base, idx);
+      bool ok = in_range && lookup<W>(r, a, ranks, cnt, idx);
       // packed -> Eq. (2)
       uint64_t outlab = 0;
       const W mask = (W(1) << a.b) - 1;
@@ -387,20 +430,69 @@ unsigned grid_for(uint64_t n, int threads = kThreads, unsigned cap = 65536u * 4)
   return (unsigned)std::min<uint64_t>(g, cap);
 }
 
-int max_lds_bytes() {
-  static int v = -1;
-  if (v < 0) {
-    int dev = 0, x = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&x, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && x > 0)
-      v = std::min(x, 65536);
-    else
-      v = 65536;
+constexpr size_t kLdsLimit = 65536;
+// dynamic LDS that leaves three workgroups of kOrbitThreads to a CU
+constexpr size_t kLdsSoft = 36 * 1024;
+
+// One launch of an orbit-search kernel template K<W, GW, PLAIN, TABS>.
+#define FTLM_LAUNCH_ORBIT(K, s, static_lds, grid, st, a, ...)                                                  \
+  {                                                                                                            \
+    const OrbitLds ol = orbit_lds(s, kLdsSoft, kLdsLimit - (static_lds));                                      \
+    (a).n_lds = ol.n_lds;                                                                                      \
+    FTLM_DISPATCH_ORBIT((s).wide, (s).plain(), (s).gw, {                                                                    \
+      if (ol.tabs)                                                                                             \
+        hipLaunchKernelGGL((K<W, GW, PLAIN, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, __VA_ARGS__);   \
+      else                                                                                                     \
+        hipLaunchKernelGGL((K<W, GW, PLAIN, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, __VA_ARGS__);  \
+    });                                                                                                        \
+    FTLM_HIP(hipGetLastError());                                                                               \
   }
-  return v;
+
+void orbit_args(const Sector& s, SecArgs& a) {
+  a.mask = s.d_mask();
+  a.img = s.d_img();
+  a.split = s.d_split();
+  a.nH = s.fac_nH;
+  a.nT = s.fac_nT;
+  a.nch = s.nch;
+  a.NC = s.NC;
+  a.cnt = s.d_cnt.p;
+  a.cnt_stride = s.cnt_stride;
+  a.N = s.N;
+  a.b = s.bits;
+  a.d = s.d;
+  a.A = s.A;
+  a.G = s.G->order;
+  a.zf = s.zflip ? 1 : 0;
+  a.full = s.full;
+  a.D_M = s.D_M;
+  a.n_words = s.n_words;
+  a.n_reps = s.n_reps;
+  // the sites that some element moves to the highest one
+  std::vector<char> reach(s.N, 0);
+  for (int g = 0; g < s.G->order; ++g)
+    for (int k = 0; k < s.N; ++k)
+      if (s.G->perms[(size_t)g * s.N + k] == s.N - 1) reach[k] = 1;
+  a.transitive = std::count(reach.begin(), reach.end(), 1) == s.N;
 }
 
 }  // namespace
+
+// Mask positions are read by every search, so at least two stay in LDS; the
+// counts and image tables (read once or twice per search, at lane-dependent
+// rows) join them where both fit; more positions take what is left up to the
+// soft limit, which keeps three workgroups on a CU.
+OrbitLds orbit_lds(const Sector& s, size_t soft, size_t limit) {
+  OrbitLds o;
+  const size_t pos = (size_t)s.NC * 16 * s.gw * 8;
+  const size_t tabs = (size_t)(s.N + 1) * s.cnt_stride * 8 + s.img_bytes;
+  o.tabs = tabs + 2 * pos <= limit;
+  const size_t rest = o.tabs ? tabs : 0;
+  const size_t room = std::max(std::min(soft, limit), std::min(limit, rest + 4 * pos));
+  o.n_lds = room > rest ? (int)std::min<size_t>((size_t)s.N, (room - rest) / pos) : 0;
+  o.bytes = rest + (size_t)o.n_lds * pos;
+  return o;
+}
 
 std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<const Group> G, int two_M,
                                      const ftlm_opts* opts) {
@@ -419,7 +511,9 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
   while ((1 << s.bits) < s.d) ++s.bits;
   if (s.N * s.bits > 64) fail(FTLM_ERR_UNSUPPORTED, "packed labels need more than 64 bits");
   s.wide = s.N * s.bits > 32;
-  s.nch = nch_bucket((s.N * s.bits + 3) / 4);
+  s.nch = (s.N * s.bits + 3) / 4;
+  s.NC = (s.N + 3) / 4;
+  s.gw = orbit_words(G->order);
   // spin flip (G x Z2) at M = 0
   s.zflip = opts && opts->spin_flip;
   if (s.zflip && two_M != 0) fail(FTLM_ERR_INVALID_ARG, "the spin flip resolves only the M = 0 sector");
@@ -478,9 +572,9 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     s.D_M = s.cnt[(size_t)s.N * s.cnt_stride + s.A];
   }
   s.n_words = (s.D_M + 63) / 64;
-  // permutation chunk tables of the factored group (dev::OrbitTabs layout):
-  // all |G| elements when their tables take at most 16 KiB, otherwise
-  // G = T H with |H| + |T| tables
+  // orbit-search tables (dev::Orbit): candidate masks, image tables of all |G|
+  // elements when these take at most 16 KiB and of G = T H with |H| + |T|
+  // tables otherwise, and each element's (t, h)
   const int G_ = G->order;
   const size_t wbytes = s.wide ? 8 : 4;
   std::vector<uint8_t> tab_host;                 // host copies of tables in flight to the device
@@ -491,9 +585,19 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     s.fac_nH = (int)fz.H.size();
     s.fac_nT = (int)fz.T.size();
     const size_t rows = (size_t)s.fac_nH + s.fac_nT;
-    const size_t tab_bytes = rows * s.nch * 16 * wbytes + fz.gidx.size() * 2;
-    s.tab_words = (uint32_t)((tab_bytes + wbytes - 1) / wbytes);
-    std::vector<uint8_t> bytes(s.tab_words * wbytes, 0);
+    s.mask_words = (size_t)s.N * s.NC * 16 * s.gw;
+    s.img_bytes = (rows * s.nch * 16 * wbytes + 7) / 8 * 8;
+    std::vector<uint8_t> bytes(s.mask_words * 8 + s.img_bytes + (size_t)G_ * 4, 0);
+    uint64_t* mask = (uint64_t*)bytes.data();
+    for (int g = 0; g < G_; ++g)
+      for (int site = 0; site < s.N; ++site) {
+        // site `site` goes to position p (sites from the highest down)
+        const int p = s.N - 1 - G->perms[(size_t)g * s.N + site];
+        uint64_t* m = mask + ((size_t)p * s.NC + site / 4) * 16 * s.gw;
+        for (int v = 0; v < 16; ++v)
+          if ((v >> (site % 4)) & 1) m[(size_t)v * s.gw + g / 64] |= 1ull << (g % 64);
+      }
+    uint8_t* img_at = bytes.data() + s.mask_words * 8;
     for (size_t row = 0; row < rows; ++row) {
       const int g = row < (size_t)s.fac_nH ? fz.H[row] : fz.T[row - s.fac_nH];
       const int32_t* p = &G->perms[(size_t)g * s.N];
@@ -509,14 +613,16 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
           }
           const size_t at = ((row * s.nch + c) * 16 + v) * wbytes;
           if (s.wide) {
-            std::memcpy(&bytes[at], &img, 8);
+            std::memcpy(img_at + at, &img, 8);
           } else {
             const uint32_t i32 = (uint32_t)img;
-            std::memcpy(&bytes[at], &i32, 4);
+            std::memcpy(img_at + at, &i32, 4);
           }
         }
     }
-    std::memcpy(&bytes[rows * s.nch * 16 * wbytes], fz.gidx.data(), fz.gidx.size() * 2);
+    uint32_t* split = (uint32_t*)(img_at + s.img_bytes);
+    for (int t = 0; t < s.fac_nT; ++t)
+      for (int h = 0; h < s.fac_nH; ++h) split[fz.gidx[(size_t)t * s.fac_nH + h]] = (uint32_t)t << 16 | (uint32_t)h;
     s.d_tab.alloc((bytes.size() + 7) / 8);
     FTLM_HIP(hipMemcpyAsync(s.d_tab.p, bytes.data(), bytes.size(), hipMemcpyHostToDevice, st));
     tab_host.swap(bytes);  // kept until the stream has passed the copy
@@ -539,25 +645,8 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
       }
     s.d_fac.upload_async(fac, st);
   }
-  const size_t tab_bytes = (size_t)s.tab_words * wbytes;
-  const bool lds = tab_bytes <= (size_t)max_lds_bytes();
   SecArgs a{};
-  a.tab = s.d_tab.p;
-  a.cnt = s.d_cnt.p;
-  a.cnt_stride = s.cnt_stride;
-  a.N = s.N;
-  a.b = s.bits;
-  a.d = s.d;
-  a.A = s.A;
-  a.G = G_;
-  a.zf = s.zflip ? 1 : 0;
-  a.full = s.full;
-  a.nH = s.fac_nH;
-  a.nT = s.fac_nT;
-  a.D_M = s.D_M;
-  a.n_words = s.n_words;
-  a.tab_words = s.tab_words;
-  const size_t shm = lds ? tab_bytes : 0;
+  orbit_args(s, a);
   FlipArgs f{s.d_bonds.p, s.d_J.p, s.nbonds};
 
   if (s.D_M == 0) {
@@ -569,33 +658,51 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
   }
   const int64_t limit = opts ? opts->hbm_limit_bytes : 0;
   // representatives
-  s.d_rank_bits.alloc(s.n_words);
-  FTLM_DISPATCH_NCH(s.nch, {
-    if (lds)
-      hipLaunchKernelGGL((k_enum<W, NCH, true>), dim3(grid_for(s.n_words)), dim3(kThreads), shm, st, a, s.d_rank_bits.p);
-    else
-      hipLaunchKernelGGL((k_enum<W, NCH, false>), dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, a, s.d_rank_bits.p);
-  });
-  FTLM_HIP(hipGetLastError());
+  DevBuf<uint64_t> rank_bits;
+  rank_bits.alloc(s.n_words);
+  // one thread per word once the words fill the device (256 CUs x 1,024
+  // threads); below that one wave per word: a sector of 924 states (15 words)
+  // took 200 us with 15 threads stepping through 64 labels each
+  const bool by_wave = s.n_words < (1ull << 18);
+  {
+    const OrbitLds ol = orbit_lds(s, kLdsSoft, kLdsLimit);
+    a.n_lds = ol.n_lds;
+    const unsigned grid = grid_for(by_wave ? s.n_words * 64 : s.n_words, kOrbitThreads, 8192);
+    FTLM_DISPATCH_ORBIT(s.wide, s.plain(), s.gw, {
+      if (by_wave && ol.tabs)
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+      else if (by_wave)
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+      else if (ol.tabs)
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+      else
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+    });
+    FTLM_HIP(hipGetLastError());
+  }
   {
     DevBuf<uint64_t> tmp;
     tmp.alloc(s.n_words);
-    hipLaunchKernelGGL(k_popcount, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, s.d_rank_bits.p, tmp.p, s.n_words);
+    hipLaunchKernelGGL(k_popcount, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, rank_bits.p, tmp.p, s.n_words);
     uint64_t total = 0;
     scan_exclusive_u64(tmp.p, tmp.p, s.n_words, &total, st);
     if (total >= 0xFFFFFFFFull) fail(FTLM_ERR_UNSUPPORTED, "more than 2^32 - 1 representatives");
     s.n_reps = total;
-    s.d_rank_base.alloc(s.n_words);
-    hipLaunchKernelGGL(k_to_u32, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, tmp.p, s.d_rank_base.p, s.n_words);
+    s.d_ranks.alloc(s.n_words);
+    hipLaunchKernelGGL(k_rank_words, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, rank_bits.p, tmp.p, s.d_ranks.p,
+                       s.n_words);
     FTLM_HIP(hipGetLastError());
     FTLM_HIP(hipStreamSynchronize(st));
+    rank_bits.release();
   }
   a.n_reps = s.n_reps;
   s.d_reps.alloc(s.n_reps);
-  FTLM_DISPATCH_NCH(s.nch, {
-    hipLaunchKernelGGL((k_extract<W>), dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, a, s.d_rank_bits.p,
-                       s.d_rank_base.p, s.d_reps.p);
-  });
+  if (s.wide)
+    hipLaunchKernelGGL((k_extract<uint64_t>), dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, a, s.d_ranks.p,
+                       s.d_reps.p);
+  else
+    hipLaunchKernelGGL((k_extract<uint32_t>), dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, a, s.d_ranks.p,
+                       s.d_reps.p);
   FTLM_HIP(hipGetLastError());
 
   // stabilizers: flags -> compaction -> host interning in first-appearance order
@@ -603,13 +710,7 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     DevBuf<uint64_t> pos;
     pos.alloc(s.n_reps + 1);
     FTLM_HIP(hipMemsetAsync(pos.p + s.n_reps, 0, sizeof(uint64_t), st));
-    FTLM_DISPATCH_NCH(s.nch, {
-      if (lds)
-        hipLaunchKernelGGL((k_stab_flag<W, NCH, true>), dim3(grid_for(s.n_reps)), dim3(kThreads), shm, st, a, s.d_reps.p, pos.p);
-      else
-        hipLaunchKernelGGL((k_stab_flag<W, NCH, false>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, s.d_reps.p, pos.p);
-    });
-    FTLM_HIP(hipGetLastError());
+    FTLM_LAUNCH_ORBIT(k_stab_flag, s, 0, grid_for(s.n_reps, kOrbitThreads, 8192), st, a, s.d_reps.p, pos.p);
     uint64_t n_nt = 0;
     scan_exclusive_u64(pos.p, pos.p, s.n_reps + 1, &n_nt, st);
     const int mw = (s.gorder + 63) / 64;
@@ -617,15 +718,8 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     masks.alloc(std::max<uint64_t>(n_nt, 1) * mw);
     idx.alloc(std::max<uint64_t>(n_nt, 1));
     if (n_nt) {
-      FTLM_DISPATCH_NCH(s.nch, {
-        if (lds)
-          hipLaunchKernelGGL((k_stab_mask<W, NCH, true>), dim3(grid_for(s.n_reps)), dim3(kThreads), shm, st, a, s.d_reps.p,
-                             pos.p, mw, masks.p, idx.p);
-        else
-          hipLaunchKernelGGL((k_stab_mask<W, NCH, false>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, s.d_reps.p,
-                             pos.p, mw, masks.p, idx.p);
-      });
-      FTLM_HIP(hipGetLastError());
+      FTLM_LAUNCH_ORBIT(k_stab_mask, s, 0, grid_for(s.n_reps, kOrbitThreads, 8192), st, a, s.d_reps.p, pos.p, mw, masks.p,
+                        idx.p);
     }
     DevBuf<unsigned long long> first;
     first.alloc(1);
@@ -689,10 +783,12 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
   s.d_ediag.alloc(s.n_reps);
   s.d_row_ptr.alloc(s.n_reps + 1);
   FTLM_HIP(hipMemsetAsync(s.d_row_ptr.p + s.n_reps, 0, sizeof(uint64_t), st));
-  FTLM_DISPATCH_NCH(s.nch, {
-    hipLaunchKernelGGL((k_entry_count<W>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, f, s.d_reps.p,
+  if (s.wide)
+    hipLaunchKernelGGL((k_entry_count<uint64_t>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, f, s.d_reps.p,
                        s.d_row_ptr.p, s.d_ediag.p);
-  });
+  else
+    hipLaunchKernelGGL((k_entry_count<uint32_t>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, f, s.d_reps.p,
+                       s.d_row_ptr.p, s.d_ediag.p);
   FTLM_HIP(hipGetLastError());
   uint64_t n_ent = 0;
   scan_exclusive_u64(s.d_row_ptr.p, s.d_row_ptr.p, s.n_reps + 1, &n_ent, st);
@@ -734,17 +830,17 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     } else {
       s.d_entries.alloc(n_ent);
     }
-    FTLM_DISPATCH_NCH(s.nch, {
-      if (lds)
-        hipLaunchKernelGGL((k_entry_fill<W, NCH, true>), dim3(grid_for(s.n_reps)), dim3(kThreads), shm, st, a, f,
-                           s.d_reps.p, s.d_row_ptr.p, s.d_rank_bits.p, s.d_rank_base.p, s.d_entries.p, s.d_eidx.p,
-                           s.d_ehc.p, s.ent_hbits, s.d_stab_id.p, (uint16_t)s.trivial_sid);
-      else
-        hipLaunchKernelGGL((k_entry_fill<W, NCH, false>), dim3(grid_for(s.n_reps)), dim3(kThreads), 0, st, a, f,
-                           s.d_reps.p, s.d_row_ptr.p, s.d_rank_bits.p, s.d_rank_base.p, s.d_entries.p, s.d_eidx.p,
-                           s.d_ehc.p, s.ent_hbits, s.d_stab_id.p, (uint16_t)s.trivial_sid);
-    });
-    FTLM_HIP(hipGetLastError());
+    // representatives per workgroup: about two full rounds of its lanes (7%
+    // under, as row lengths vary), fewer where the sector would leave the
+    // device idle
+    const double per_rep = std::max(1.0, (double)n_ent / (double)s.n_reps);
+    const int64_t list_cap = std::max<int64_t>(1, kFillList / std::max(1, 2 * s.nbonds));
+    const int rb = (int)std::max<int64_t>(
+        1, std::min<int64_t>({(int64_t)kFillReps, list_cap, (int64_t)(0.93 * 2 * kOrbitThreads / per_rep),
+                              (int64_t)(s.n_reps / 512)}));
+    const size_t fill_lds = kFillList * 4 + (kFillReps + 1) * 4 + kFillReps * 8 + 64;
+    FTLM_LAUNCH_ORBIT(k_entry_fill, s, fill_lds, grid_for((s.n_reps + rb - 1) / rb, 1, 8192), st, a, f, rb, s.d_reps.p,
+                      s.d_row_ptr.p, s.d_ranks.p, s.d_entries.p, s.d_eidx.p, s.d_ehc.p, s.ent_hbits);
   }
   FTLM_HIP(hipStreamSynchronize(st));
   return S;
@@ -754,40 +850,10 @@ void sector_canonicalize(const Sector& s, const uint64_t* labels, int64_t n, uin
                          int64_t* index, hipStream_t st) {
   if (n < 0 || (n > 0 && (!labels || !rep || !h || !index))) fail(FTLM_ERR_INVALID_ARG, "bad canonicalize arguments");
   if (n == 0) return;
+  // (an empty sector: nothing is in range; the search for rep and h still runs)
   SecArgs a{};
-  a.tab = s.d_tab.p;
-  a.cnt = s.d_cnt.p;
-  a.cnt_stride = s.cnt_stride;
-  a.N = s.N;
-  a.b = s.bits;
-  a.d = s.d;
-  a.A = s.A;
-  a.G = s.G->order;
-  a.zf = s.zflip ? 1 : 0;
-  a.full = s.full;
-  a.nH = s.fac_nH;
-  a.nT = s.fac_nT;
-  a.D_M = s.D_M;
-  a.n_words = s.n_words;
-  a.n_reps = s.n_reps;
-  a.tab_words = s.tab_words;
-  const size_t tab_bytes = (size_t)s.tab_words * (s.wide ? 8 : 4);
-  const bool lds = tab_bytes <= (size_t)max_lds_bytes();
-  const uint64_t* bits = s.d_rank_bits.p;
-  const uint32_t* base = s.d_rank_base.p;
-  if (s.D_M == 0) {
-    // empty sector: nothing is in range; still run the search for rep/h
-    a.D_M = 0;
-  }
-  FTLM_DISPATCH_NCH(s.nch, {
-    if (lds)
-      hipLaunchKernelGGL((k_canon_labels<W, NCH, true>), dim3(grid_for((uint64_t)n)), dim3(kThreads), tab_bytes, st, a,
-                         bits, base, labels, n, rep, h, index);
-    else
-      hipLaunchKernelGGL((k_canon_labels<W, NCH, false>), dim3(grid_for((uint64_t)n)), dim3(kThreads), 0, st, a, bits,
-                         base, labels, n, rep, h, index);
-  });
-  FTLM_HIP(hipGetLastError());
+  orbit_args(s, a);
+  FTLM_LAUNCH_ORBIT(k_canon_labels, s, 0, grid_for((uint64_t)n, kOrbitThreads, 8192), st, a, s.d_ranks.p, labels, n, rep, h, index);
 }
 
 std::vector<uint64_t> sector_export_labels(const Sector& s) {
