@@ -315,9 +315,9 @@ typedef struct ftlm_hv_opts {
   double shift;           /* the call applies H - shift (0: H) */
   int32_t lanes_used;     /* out: lanes per representative of the launch */
   int32_t adjacent_columns; /* out: 1 when the launch ran the kernel whose lanes hold
-                             adjacent columns (padded rows, d_Gamma equal to its kernel
-                             bucket 1..6, nvec a whole number of column tiles): the
-                             kernel of ftlm_run's large blocks */
+                             adjacent columns on padded rows (d_Gamma equal to its
+                             kernel bucket 1..6, at least as many vectors as one lane
+                             holds): the kernel of ftlm_run's large blocks */
   int64_t reserved[4];
 } ftlm_hv_opts;
 

@@ -37,10 +37,17 @@ __global__ void __launch_bounds__(256) k_rep_counts(const uint16_t* __restrict__
   if (threadIdx.x == 0) atomicAdd(n_active, red[0]);
 }
 
-__global__ void k_meta(const uint64_t* __restrict__ off, const uint16_t* __restrict__ stab_id, uint64_t n,
-                       uint64_t* __restrict__ meta) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+// off has n + 1 elements (off[n] = D).
+__global__ void k_meta(const uint64_t* __restrict__ off, const uint16_t* __restrict__ stab_id, uint64_t n, uint32_t d,
+                       uint64_t* __restrict__ meta, uint32_t* __restrict__ lack) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
     meta[i] = off[i] | ((uint64_t)stab_id[i] << 48);
+    if ((i & 31) == 0) {
+      const uint64_t end = min(i + 32, n);
+      const uint64_t l = i * d - off[i];
+      lack[i >> 5] = off[end] - off[i] == (end - i) * d && l < 0x80000000ull ? (uint32_t)l : 0x80000000u;
+    }
+  }
 }
 
 unsigned grid1(uint64_t n) {
@@ -245,24 +252,38 @@ std::unique_ptr<Block> build_block(std::shared_ptr<Sector> sec, int irrep, int r
   // only the |G| matrices of G: the flipped half is parity * rho(g), applied
   // by the kernel as a sign on the coefficient
   B->fpar = parity;
-  std::vector<double> rt((size_t)n * dp * dp, 0.0);
+  auto align16 = [](size_t x) { return (x + 15) / 16 * 16; };
+  const size_t nv = (size_t)std::max(ns, 1);
+  const size_t o_stab = align16((size_t)n * dp * dp * 8), o_J = align16(o_stab + nv * 32),
+               o_fac = align16(o_J + (size_t)sec->nbonds * 8), o_bonds = align16(o_fac + sec->fac.size() * 8),
+               o_V = align16(o_bonds + (size_t)sec->nbonds * 8), end = align16(o_V + nv * dp * dp * 8);
+  if (end >= (1ull << 32)) fail(FTLM_ERR_UNSUPPORTED, "irrep tables above 4 GiB");
+  B->o_stab = (uint32_t)o_stab;
+  B->o_J = (uint32_t)o_J;
+  B->o_fac = (uint32_t)o_fac;
+  B->o_bonds = (uint32_t)o_bonds;
+  B->o_V = (uint32_t)o_V;
+  B->small_bytes = (uint32_t)end;
+  std::vector<uint8_t> small(end, 0);
+  double* rt = (double*)small.data();
   for (int g = 0; g < n; ++g)
     for (int be = 0; be < d; ++be)
       for (int ga = 0; ga < d; ++ga) rt[((size_t)g * dp + be) * dp + ga] = B->rho[((size_t)g * d + ga) * d + be];
-  B->d_rhoT64.upload_async(rt, st);
-  std::vector<double> vp((size_t)std::max(ns, 1) * dp * dp, 0.0);
+  double* vp = (double*)(small.data() + o_V);
   for (int s = 0; s < ns; ++s)
     for (int i = 0; i < d; ++i)
       for (int k = 0; k < d; ++k) vp[((size_t)s * dp + i) * dp + k] = B->V_stab[((size_t)s * d + i) * d + k];
-  B->d_V64.upload_async(vp, st);
-  std::vector<double> sf((size_t)std::max(ns, 1) * 4, 0.0);
+  double* sf = (double*)(small.data() + o_stab);
   for (int s = 0; s < ns; ++s) {
     sf[4 * s + 0] = B->n_stab[s];
     sf[4 * s + 1] = std::sqrt(B->L_stab[s]);
     sf[4 * s + 2] = 1.0 / std::sqrt(B->L_stab[s]);
     sf[4 * s + 3] = B->trivial[s];
   }
-  B->d_stabf64.upload_async(sf, st);
+  std::memcpy(small.data() + o_J, sec->J.data(), (size_t)sec->nbonds * 8);
+  std::memcpy(small.data() + o_fac, sec->fac.data(), sec->fac.size() * 8);
+  std::memcpy(small.data() + o_bonds, sec->bonds.data(), (size_t)sec->nbonds * 8);
+  B->d_small.upload_async(small, st);
   DevBuf<uint8_t> d_n;
   DevBuf<unsigned long long> per;
   DevBuf<uint64_t> off;
@@ -278,8 +299,9 @@ std::unique_ptr<Block> build_block(std::shared_ptr<Sector> sec, int irrep, int r
     FTLM_HIP(hipGetLastError());
     scan_exclusive_u64(off.p, off.p, sec->n_reps + 1, nullptr, st);
     B->d_meta.alloc(sec->n_reps);
+    B->d_lack.alloc((sec->n_reps + 31) / 32);
     hipLaunchKernelGGL(k_meta, dim3(grid1(sec->n_reps)), dim3(256), 0, st, off.p, sec->d_stab_id.p, sec->n_reps,
-                       B->d_meta.p);
+                       (uint32_t)d, B->d_meta.p, B->d_lack.p);
     FTLM_HIP(hipGetLastError());
   }
   FTLM_HIP(hipStreamSynchronize(st));

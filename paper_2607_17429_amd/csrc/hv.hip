@@ -17,6 +17,11 @@ namespace {
 constexpr uint32_t kSmallLdsBudget = 48 * 1024;
 constexpr uint32_t kLdsLimit = 65536 - 2048;  // dynamic LDS; 2 KiB stay for the epilogue reduction
 
+// lanes of a launch up to which a wave seldom shares its SIMD (256 CUs x 4
+// SIMDs x 64 lanes x 2): several slices in flight per group then hide what
+// other waves cannot
+constexpr uint64_t kDeepLanes = 131072;
+
 struct Layout {
   int GL, log2GL, VPL, tile_w, tiles;
 };
@@ -35,18 +40,34 @@ int vpl_bucket(int need, bool otf) {
   return 8;
 }
 
-// Lanes per output representative (GL) and vectors per lane (VPL).  Default
-// (measured on MI355X for the s=1/2 icosidodecahedron H_g block): one lane per
-// vector up to 4 vectors, then about 3 vectors per lane, which keeps 64/GL
-// representatives in flight per wave.  gl > 0 forces GL (the autotuner's choice).
-Layout choose_layout(int nvec, bool otf, int gl = 0) {
+// Whether the adjacent-column kernels can run the block (hv_setup's rule)
+bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && b.dg == b.dgp && b.dgp <= 6; }
+
+// Default lanes per output representative.  A sector of up to 4,096
+// representatives takes 32 whatever the vectors: its few waves wait for one
+// another's flips, not for lanes, and 32 lanes decode a whole row of flips at
+// once (dodecahedron H_g at M = 0, 1,648 representatives, FP64: 24 vectors 19
+// us against 40 with 8 lanes, one vector 19 against 36 us with one lane).
+// Above (measured on MI355X on the s = 1/2 icosidodecahedron at M = 0): up to 4 vectors one lane that holds them all
+// where the sector has enough representatives to fill the device that way
+// (2 FP32 vectors, d = 5: 0.66 against 0.70 ms with two lanes), one lane per
+// vector otherwise; above, about 3 vectors per lane, or 6 in FP16 (whose rows
+// are then whole 4-byte words; 24 vectors, d = 3: 1.40 against 1.67 ms) where
+// half as many lanes still fill the device (a sector of a few thousand
+// representatives took 42 us with 6 per lane, 24 us with 3).
+int default_lanes(const Block& b, int nvec, int dtype) {
+  if (b.sec->hv_mode != FTLM_HV_ONTHEFLY && adjacent_ok(b) && nvec <= 32 && b.sec->n_reps * 32 <= kDeepLanes) return 32;
+  if (b.sec->hv_mode == FTLM_HV_ONTHEFLY)
+    return nvec <= 4 ? pow2_at_least(nvec) : std::min(16, pow2_at_least((nvec + 3) / 4));
+  if (nvec <= 4) return adjacent_ok(b) && b.sec->n_reps >= (1u << 17) ? 1 : pow2_at_least(nvec);
+  if (dtype == FTLM_F16 && adjacent_ok(b) && b.sec->n_reps >= (1u << 16)) return pow2_at_least((nvec + 5) / 6);
+  return pow2_at_least((nvec + 2) / 3);
+}
+
+// Lanes per output representative (GL) and vectors per lane (VPL) for gl lanes
+// (the autotuner's choice or the default).
+Layout choose_layout(int nvec, bool otf, int gl) {
   Layout L{};
-  if (gl <= 0) {
-    if (nvec <= 4)
-      gl = pow2_at_least(nvec);
-    else
-      gl = otf ? std::min(16, pow2_at_least((nvec + 3) / 4)) : pow2_at_least((nvec + 2) / 3);
-  }
   L.GL = std::min(64, pow2_at_least(gl));
   L.VPL = vpl_bucket((std::min(nvec, 64 * 8) + L.GL - 1) / L.GL, otf);
   if (L.GL * L.VPL > 64 && L.GL > 1) {
@@ -60,11 +81,23 @@ Layout choose_layout(int nvec, bool otf, int gl = 0) {
   return L;
 }
 
-dim3 hv_grid(const Block& b, const Layout& L) {
+struct Sweep {
+  uint32_t w, k;  // workgroups and rounds of one sweep
+  dim3 grid;
+};
+
+Sweep hv_grid(const Block& b, const Layout& L) {
+  constexpr uint64_t TW = 64;    // workgroups of a sweep
+  constexpr uint64_t TG = 8064;  // workgroups asked for: the grid stays within 8192
   const uint64_t slots_per_block = (uint64_t)(kThreads / 64) * (64 / L.GL);
-  uint64_t gx = (b.sec->n_reps + slots_per_block - 1) / slots_per_block;
-  gx = std::max<uint64_t>(1, std::min<uint64_t>(gx, 8192));
-  return dim3((unsigned)gx, (unsigned)L.tiles, 1);
+  const uint64_t need = std::max<uint64_t>(1, (b.sec->n_reps + slots_per_block - 1) / slots_per_block);
+  Sweep s{};
+  s.k = (uint32_t)((need + TG - 1) / TG);
+  const uint64_t per_xcd = ((need + s.k - 1) / s.k + 7) / 8;
+  const uint64_t sweeps = (per_xcd + TW - 1) / TW;
+  s.w = (uint32_t)((per_xcd + sweeps - 1) / sweeps);
+  s.grid = dim3((unsigned)(8 * sweeps * s.w), (unsigned)L.tiles, 1);
+  return s;
 }
 
 uint32_t align16(uint64_t x) { return (uint32_t)((x + 15u) & ~uint64_t(15)); }
@@ -103,7 +136,8 @@ TuneKey tune_key(const Block& b, int nvec, int dtype, const VecLayout& vl, bool 
 }
 
 int tuned_gl(const Block& b, int nvec, int dtype, const VecLayout& vl, bool epi) {
-  return tune_lookup(tune_key(b, nvec, dtype, vl, epi));
+  const int gl = tune_lookup(tune_key(b, nvec, dtype, vl, epi));
+  return gl > 0 ? gl : default_lanes(b, nvec, dtype);
 }
 
 // Column sums of a (ng x nvec) array of per-workgroup partials, one workgroup
@@ -144,7 +178,7 @@ int hv_layout_lanes(const Block& b, int nvec, int dtype, const VecLayout& vl, bo
 }
 
 int hv_partial_groups(const Block& b, int nvec, int gl) {
-  return (int)hv_grid(b, choose_layout(nvec, b.sec->hv_mode == FTLM_HV_ONTHEFLY, gl)).x;
+  return (int)hv_grid(b, choose_layout(nvec, b.sec->hv_mode == FTLM_HV_ONTHEFLY, gl)).grid.x;
 }
 
 void apply_hv(const Block& b, const void* X, void* Y, int nvec, int64_t ld, int dtype, hipStream_t st,
@@ -227,7 +261,7 @@ HvExPlan plan_hv_ex(const Block& b, int nvec, int64_t ld, int dtype, const ftlm_
     LaunchCfg c{};
     HvArgs<double> a{};
     hv_setup(b, nvec, nvec, p.gl, p.vl, nullptr, c, a);
-    p.adjacent = c.contig && c.slds && !c.otf && b.dgp <= 6;
+    p.adjacent = p.vl.pad && c.var != kGeneral && c.slds;
   }
   return p;
 }
@@ -263,25 +297,21 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   const bool otf = s.hv_mode == FTLM_HV_ONTHEFLY;
   const Layout L = choose_layout(nvec, otf, gl);
   c = LaunchCfg{};
-  c.grid = hv_grid(b, L);
+  const Sweep sw = hv_grid(b, L);
+  c.grid = sw.grid;
   c.otf = otf;
   c.wide = s.wide;
   c.gw = s.gw;
   c.vpl = L.VPL;
-  // kernels specialised for the dense gather (table-driven H.V only)
-  c.contig = pad && !otf && b.dg == b.dgp && nvec == L.tile_w * L.tiles;
-  const uint64_t DG = (uint64_t)b.dgp;
-  const uint64_t ns = (uint64_t)std::max(s.n_stab, 1);
+  // adjacent columns wherever a gathered row is whole (no row of the bucket
+  // beyond d_Gamma) and every lane can own VPL columns
+  c.var = !adjacent_ok(b) || nvec < L.VPL ? kGeneral
+          : L.GL == 1 && L.tiles == 1 && L.VPL <= 4 && nvec == L.VPL ? kNarrow
+          : L.VPL <= 4 && s.n_reps * (uint64_t)L.GL * L.tiles <= kDeepLanes ? kDeep : kAdjacent;
   // small tables first priority; the orbit search's tables take what they
   // leave (up to the soft limit that keeps two workgroups on a CU), the rest
   // of them is read through the caches
-  uint64_t small = 0;
-  small = align16(small + (uint64_t)s.G->order * (uint64_t)b.dgp * b.dgp * 8);
-  small = align16(small + (uint64_t)std::max(s.n_stab, 1) * b.dgp * b.dgp * 8);
-  small = align16(small + (uint64_t)std::max(s.n_stab, 1) * 4 * 8);
-  small = align16(small + (uint64_t)s.nbonds * 8);
-  small = align16(small + (uint64_t)(2 * s.d * s.d) * 8);
-  small = align16(small + (uint64_t)s.nbonds * 2 * 4);
+  const uint64_t small = b.small_bytes;
   OrbitLds ol;
   if (otf) {
     const size_t room = kLdsLimit - 32 - (small <= kSmallLdsBudget ? small : 0);
@@ -290,41 +320,13 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   c.lds_tab = ol.tabs;
   c.plain = s.plain() && s.gw <= 5 && ol.tabs;
   const uint32_t base = align16(ol.bytes);
-  uint64_t o = base;
-  const uint32_t o_rho = (uint32_t)o;
-  o = align16(o + (uint64_t)s.G->order * DG * DG * 8);
-  const uint32_t o_V = (uint32_t)o;
-  o = align16(o + ns * DG * DG * 8);
-  const uint32_t o_stab = (uint32_t)o;
-  o = align16(o + ns * 4 * 8);
-  const uint32_t o_J = (uint32_t)o;
-  o = align16(o + (uint64_t)s.nbonds * 8);
-  const uint32_t o_fac = (uint32_t)o;
-  o = align16(o + (uint64_t)(2 * s.d * s.d) * 8);
-  const uint32_t o_bonds = (uint32_t)o;
-  o = align16(o + (uint64_t)s.nbonds * 2 * 4);
-  c.slds = (o - base) <= kSmallLdsBudget && o <= kLdsLimit;
-  c.shm = c.slds ? o : base;
-  c.vg = false;
-  uint32_t vg_stab = 0, vg_J = 0, vg_fac = 0, vg_bonds = 0;
-  if (!c.slds && !otf) {
-    // the kernels without V_S in LDS (VG): rho^T and the small tables only;
-    // V_S, used only for non-trivial stabilizers, is read through the caches
-    // (a 6x6-torus sector has up to 324 stabilizer types)
-    uint64_t v = align16(base + (uint64_t)s.G->order * DG * DG * 8);
-    vg_stab = (uint32_t)v;
-    v = align16(v + ns * 4 * 8);
-    vg_J = (uint32_t)v;
-    v = align16(v + (uint64_t)s.nbonds * 8);
-    vg_fac = (uint32_t)v;
-    v = align16(v + (uint64_t)(2 * s.d * s.d) * 8);
-    vg_bonds = (uint32_t)v;
-    v = align16(v + (uint64_t)s.nbonds * 2 * 4);
-    if ((v - base) <= kSmallLdsBudget && v <= kLdsLimit) {
-      c.slds = c.vg = true;
-      c.shm = v;
-    }
-  }
+  c.slds = small <= kSmallLdsBudget && base + small <= kLdsLimit;
+  // the kernels without V_S in LDS (VG): rho^T and the small tables only;
+  // V_S, used only for non-trivial stabilizers, is read through the caches
+  // (a 6x6-torus sector has up to 324 stabilizer types)
+  c.vg = !c.slds && !otf && b.o_V <= kSmallLdsBudget;
+  if (c.vg) c.slds = true;
+  c.shm = base + (c.vg ? b.o_V : c.slds ? (uint32_t)small : 0);
   {
     a.reps = s.d_reps.p;
     a.row_ptr = s.d_row_ptr.p;
@@ -336,20 +338,23 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.dstride = b.dg;
     a.rpl = vl.rpl;
     a.rpline = vl.rpl > 1 || vl.aligned ? vl.rpline : (uint32_t)b.dg;
+    a.rows = vec_rows(b, vl);
+    a.lack = b.d_lack.p;
     a.triv_sid = s.trivial_sid;
     a.sid = s.d_stab_id.p;
     a.meta = b.d_meta.p;
     a.ediag = s.d_ediag.p;
-    a.rhoT = b.d_rhoT64.p;
-    a.V = b.d_V64.p;
-    a.stabf = b.d_stabf64.p;
-    a.bonds = s.d_bonds.p;
-    a.J = s.d_J.p;
-    a.fac = s.d_fac.p;
+    a.small = b.d_small.p;
+    a.small_bytes = c.vg ? b.o_V : b.small_bytes;
+    a.o_small = base;
+    a.o_stab = b.o_stab;
+    a.o_J = b.o_J;
+    a.o_fac = b.o_fac;
+    a.o_bonds = b.o_bonds;
+    a.o_V = b.o_V;
     a.b = s.bits;
     a.dloc = s.d;
     a.nbonds = s.nbonds;
-    a.G = s.G->order;  // rho^T tables: one per element of G
     a.Gbase = s.G->order;
     a.fpar = b.fpar;
     a.zf = s.zflip ? 1 : 0;
@@ -362,20 +367,15 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.nT = s.fac_nT;
     a.nch = s.nch;
     a.NC = s.NC;
-    a.n_stab = (int)ns;
     a.n_reps = s.n_reps;
     a.ld = ld;
     a.nvec = nvec;
     a.GL = L.GL;
     a.log2GL = L.log2GL;
     a.tile_w = L.tile_w;
+    a.sweep_w = sw.w;
+    a.sweep_k = sw.k;
     a.zero = 0;
-    a.o_rho = o_rho;
-    a.o_V = c.vg ? 0 : o_V;
-    a.o_stab = c.vg ? vg_stab : o_stab;
-    a.o_J = c.vg ? vg_J : o_J;
-    a.o_fac = c.vg ? vg_fac : o_fac;
-    a.o_bonds = c.vg ? vg_bonds : o_bonds;
     a.cnt = s.d_cnt.p;
     a.ranks = s.d_ranks.p;
     a.cnt_stride = s.cnt_stride;

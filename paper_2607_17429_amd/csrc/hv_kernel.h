@@ -12,19 +12,29 @@
 // L = |G| / |Stab|.
 //
 // Lane layout: a group of GL lanes owns one output representative; lane g of
-// the group holds VPL vector columns (v = tile + g + j * GL, or the adjacent
-// v = tile + g * VPL + j in CONTIG launches, see hv_col_lane).  Every output
-// element is written by exactly one lane and the sum over flips runs in a
-// fixed order, so results are deterministic and do not depend on how many
-// vectors share the launch.  Small GL (8) with VPL vectors per lane keeps 64/GL
+// the group holds VPL vector columns (see HvVariant).  Every output element
+// is written by exactly one lane and the sum over flips runs in a fixed
+// order, so results are deterministic and do not depend on how many vectors
+// share the launch.  Small GL with VPL vectors per lane keeps 64/GL
 // representatives per wave in flight, which is what hides the latency of the
-// dependent loads (flip -> target metadata -> X rows): a chunk of GL flips is
-// fetched with one load per lane and exchanged by lane shuffles, then each
-// flip's n_r rows of X[r] are gathered for all VPL vectors.  rho^T, V_S, the
-// stabilizer data and the bond coefficients sit in LDS when they fit; when
-// only V_S does not (many stabilizer types), the dense-gather kernels keep
-// the others in LDS and read V_S, needed only for non-trivial stabilizers,
-// through the caches (VG; table-driven H.V only).
+// dependent loads (flip -> target -> X rows): a chunk of GL flips is fetched
+// and decoded (target offset, coefficient) with one flip per lane and
+// exchanged by lane shuffles, then each flip's rows of X[r] are gathered for
+// all VPL vectors.  rho^T, V_S, the stabilizer data and the bond coefficients
+// sit in LDS when they fit; when only V_S does not (many stabilizer types),
+// the kernels keep the others in LDS and read V_S, needed only for
+// non-trivial stabilizers, through the caches (VG; table-driven H.V only).
+//
+// What bounds it: the rate of 128-byte lines the device delivers for random
+// slices, about 5.4e10 per second whether they come from HBM or the Infinity
+// Cache, and the waves that can wait for them.  Figures (MI355X, before ->
+// after one decode per flip, four waves, adjacent columns in block rows and
+// sweeps on one XCD; icosidodecahedron M = 0, 4.02e7 flips): plain product,
+// d = 5, 24 FP32 columns 3.62 -> 2.87 ms, d = 3 3.32 -> 1.69 ms; one FP64
+// column, d = 5 1.33 -> 0.74 ms; two FP32 columns 0.91 -> 0.66 ms; 24 FP16
+// columns, d = 3 3.59 -> 1.40 ms; with the Lanczos epilogue in padded rows,
+// 24 FP32 columns, d = 5 3.34 -> 2.97 ms, d = 3 1.98 -> 1.77 ms, d = 1 0.85 ->
+// 0.79 ms.
 // Arithmetic is FP64; FP32 and FP16 storage round once on the store.
 //
 // Flips come from the sector's entry table (target index, h, flip id; built
@@ -52,14 +62,13 @@ namespace ftlm {
 namespace hvk {
 
 constexpr int kThreads = 256;
-// occupancy floor handed to the register allocator for kernels whose
-// accumulator (DG x VPL doubles) is small enough to meet it without spills
-#ifndef FTLM_HV_WAVES_PER_EU
-#define FTLM_HV_WAVES_PER_EU 4
-#endif
-#ifndef FTLM_HV_FLOOR_WIDTH
-#define FTLM_HV_FLOOR_WIDTH 10
-#endif
+// Waves per SIMD asked of the register allocator, by the accumulator's DG x
+// VPL doubles.  The gathers' latency is hidden by other waves, so four waves
+// with a few spilled registers beat three without (icosidodecahedron H_g, 24
+// FP32 columns, 15 doubles: 2.96 against 3.10 ms); at 25 to 30 doubles three
+// (six FP16 columns, d = 5: 2.50 against 2.73 ms with two); at 18 and 24 the
+// spills cost more than the wave gives (1.40 against 1.44 ms).
+constexpr int hv_waves(int width) { return width <= 15 ? 4 : width >= 25 && width <= 30 ? 3 : 1; }
 constexpr uint64_t kOffMask = (1ull << 48) - 1;
 constexpr uint32_t kInvalid = 0xffffffffu;
 
@@ -77,24 +86,23 @@ struct HvArgs {
   // target's stabilizer id comes from the entry's trivial bit or sid[]
   int pad, dstride, triv_sid;
   uint32_t rpl, rpline;
+  uint64_t rows;        // rows of X and Y
+  const uint32_t* lack; // block rows: rows missing before every 32nd representative (Block::d_lack)
   const uint16_t* sid;
   const uint64_t* meta;
   const double* ediag;
-  const double* rhoT;   // [g][beta][gamma], stride DG
-  const double* V;      // [s][gamma][k], stride DG
-  const double* stabf;  // [s][4] = n, sqrtL, 1/sqrtL, trivial
-  const int32_t* bonds;
-  const double* J;
-  const double* fac;    // [2][dloc][dloc]
-  int b, dloc, nbonds, G, n_stab;
+  // small tables (Block::d_small): bytes to stage, where they go in dynamic
+  // LDS (behind the orbit search's), offsets of the tables within
+  const uint8_t* small;
+  uint32_t small_bytes, o_small, o_stab, o_J, o_fac, o_bonds, o_V;
+  int b, dloc, nbonds;
   uint64_t n_reps;
   const T* X;
   T* Y;
   int64_t ld;
   int nvec, GL, log2GL, tile_w;
+  uint32_t sweep_w, sweep_k;  // workgroups and rounds of one sweep (see k_hv)
   int zero;  // always 0 (see the non-trivial stabilizer branch)
-  // dynamic LDS layout (byte offsets): [orbit search][rho^T][V][stab][J][fac][bonds]
-  uint32_t o_rho, o_V, o_stab, o_J, o_fac, o_bonds;
   // on-the-fly search (dev::Orbit; LDS: n_lds mask positions, counts, images)
   const uint64_t* mask;
   const void* img;
@@ -122,7 +130,7 @@ struct LaunchCfg {
   dim3 grid;
   size_t shm;
   bool otf, lds_tab, slds, wide, plain;  // lds_tab: counts and images of the search in LDS
-  bool contig;  // the dense gather holds: adjacent columns per lane
+  int var;      // HvVariant
   bool vg;      // all small tables but V_S in LDS (table-driven H.V)
   int gw, vpl;
 };
@@ -159,10 +167,11 @@ __device__ __forceinline__ _Float16 pair_swap(_Float16 v) {
   return __builtin_bit_cast(_Float16, (uint16_t)pair_swap_u32(__builtin_bit_cast(uint16_t, v)));
 }
 
-// Both columns of one row of a two-column slice, loaded as one aligned word.
-template <typename T>
-struct alignas(2 * sizeof(T)) RowPair {
-  T c0, c1;
+// Row-major elements loaded as one word of N elements at the element type's
+// alignment (global loads of up to 16 bytes need no more than that).
+template <typename T, int N>
+struct __attribute__((packed, aligned(sizeof(T)))) Elems {
+  T v[N];
 };
 
 template <typename E>
@@ -171,21 +180,6 @@ __device__ __forceinline__ const E* stage(const E* src, uint32_t count, char* ds
   for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = src[i];
   return dst;
 }
-
-// Whether a launch may take the dense gather (padded rows with d_Gamma equal
-// to the dimension bucket and full column tiles; uniform over the launch).
-template <typename T>
-__device__ __forceinline__ bool hv_dense(const HvArgs<T>& a, int DG, int VPL, int ntiles) {
-  return a.pad && a.dstride == DG && a.nvec == a.tile_w * ntiles && a.tile_w == a.GL * VPL;
-}
-
-// Column layout of a lane group.  Default: lane g holds columns g + j*GL (one
-// coalesced load per column; gathers with clamped addresses and selects do
-// not merge into wide loads).  CONTIG kernels, launched by the host only where
-// the dense gather holds: lane g holds the adjacent columns g*VPL + j, so the
-// gather of one row is one wide load per lane.
-__host__ __device__ constexpr int hv_col_lane(bool contig, int vpl) { return contig ? vpl : 1; }
-__host__ __device__ constexpr int hv_col_step(bool contig, int gl) { return contig ? 1 : gl; }
 
 struct HvTabs {
   const double* rhoT;
@@ -196,18 +190,75 @@ struct HvTabs {
   const int32_t* bonds;
 };
 
-// The H.V over the representatives p = slot, slot + slot_stride, ... of one
-// column tile: lane group of GL lanes per representative (see the file text).
-// dot[j] accumulates q_j . w of this lane's column j in the Lanczos epilogue.
+// The small tables at `base` (LDS or memory); V possibly elsewhere.
+template <typename T>
+__device__ __forceinline__ HvTabs small_tabs(const HvArgs<T>& a, const uint8_t* base, const uint8_t* vbase) {
+  return HvTabs{(const double*)base, (const double*)(vbase + a.o_V), (const double*)(base + a.o_stab),
+                (const double*)(base + a.o_J), (const double*)(base + a.o_fac), (const int32_t*)(base + a.o_bonds)};
+}
+
+// Copies bytes (a multiple of 16) into LDS with eight 16-byte loads in flight
+// per thread: table by table with one 8-byte load at a time, the staging was
+// most of a small launch (DG = 5, 36 KB: 12 us).
+__device__ __forceinline__ void stage_small(const uint8_t* src, uint32_t bytes, uint8_t* dst) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  const u4* s = (const u4*)src;
+  u4* d = (u4*)dst;
+  const uint32_t n = bytes / 16, step = blockDim.x;
+  for (uint32_t i = threadIdx.x; i < n; i += 8 * step) {
+    u4 v[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) v[u] = s[min(i + u * step, n - 1)];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u)
+      if (i + u * step < n) d[i + u * step] = v[u];
+  }
+}
+
+// Kernel variants (the host picks one, hv_setup):
+//   kGeneral   lane g of a group holds columns g + j * GL; every element of a
+//              gather has its own clamped address and a select.  Any launch.
+//   kAdjacent  lane g holds the adjacent columns g * VPL + j (the last lanes
+//              move back to end at column nvec - 1 and own only the columns
+//              no other lane has), so a gathered row is one wide load per
+//              lane.  Table-driven launches with d_Gamma equal to the
+//              dimension bucket and nvec >= VPL.
+//   kNarrow    kAdjacent with one lane per representative that holds every
+//              column: no exchange between lanes, several flips' slices in
+//              flight per lane, a slice of adjacent rows in 16-byte loads.
+//   kDeep      kAdjacent with several flips' slices in flight per lane group,
+//              for launches of so few waves that none waits for another.
+enum HvVariant { kGeneral = 0, kAdjacent = 1, kNarrow = 2, kDeep = 3 };
+
+// One flip as the gather and the accumulation need it, found by one lane:
+// the coefficient c_e / sqrt(L_r) (sign of a flipped element included), the
+// element offset of the target's first row, n_r, and h, stabilizer id, flags.
+struct Flip {
+  double c;
+  uint64_t off;   // element offset (56 bits) | n_r << 56; n_r = 0: no term
+  uint32_t info;  // h | stabilizer id << 16
+  static constexpr uint64_t kOff = (1ull << 56) - 1;
+  // flags above n_r (dimensions up to 12 need 4 bits)
+  static constexpr uint64_t kTrivial = 1ull << 60;  // trivial stabilizer
+  static constexpr uint64_t kEnd = 1ull << 61;      // rows beyond n_r may lie past the array
+  __device__ __forceinline__ int n() const { return (int)(off >> 56) & 15; }
+  __device__ __forceinline__ int h() const { return (int)(info & 0xffffu); }
+  __device__ __forceinline__ int sr() const { return (int)(info >> 16); }
+};
+
+// The H.V over the representatives p = slot, slot + slot_stride, ... < p_end of
+// one column tile: lane group of GL lanes per representative (see the file text).
+// dot[j] accumulates q_j . w of this lane's column vcol + j * (column step).
 // GW > 0: flips are found on the fly (orbit search with candidate sets of GW
 // words; osearch, ocnt: its tables); GW = 0: flips come from the entry table.
-template <typename T, int DG, int VPL, int GW, int NCH, bool CONTIG = false>
+template <typename T, int DG, int VPL, int GW, int NCH, int VAR = kGeneral>
 __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
                                         const dev::Orbit<word_t<NCH>, (GW > 0 ? GW : 1), kPlain<NCH, GW>>& osearch,
-                                        const uint64_t* ocnt, int tile, int ntiles,
-                                        uint64_t slot, uint64_t slot_stride, double (&dot)[VPL], bool (&vok)[VPL]) {
+                                        const uint64_t* ocnt, int tile, uint64_t slot, uint64_t slot_stride, uint64_t p_end,
+                                        double (&dot)[VPL], bool (&vok)[VPL], int& vcol) {
   using W = word_t<NCH>;
   constexpr bool OTF = GW > 0;
+  constexpr bool ADJ = VAR != kGeneral;
   const bool EPI = a.partials != nullptr;
   const double* rhoT = tb.rhoT;
   const double* Vt = tb.Vt;
@@ -216,26 +267,31 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
   const double* fac = tb.fac;
   const int32_t* bonds = tb.bonds;
   const int lane = threadIdx.x & 63;
-  const int GL = a.GL;
-  const int lg = lane & (GL - 1);
+  const int GL = VAR == kNarrow ? 1 : a.GL;
+  const int lg = VAR == kNarrow ? 0 : lane & (GL - 1);
   const int gbase = lane - lg;
-  // uniform: the whole launch may gather without clamps (see the gather below)
-  const bool dense = CONTIG || hv_dense(a, DG, VPL, ntiles);
-  // uniform: a pair of lanes per representative, one column each, and
-  // two-element rows that start on a two-element boundary (see the gather)
-  const bool pair_rows = CONTIG && VPL == 1 && GL == 2 && a.ld == 2 &&
-                         ((uintptr_t)a.X & (2 * sizeof(T) - 1)) == 0;
-  // lane lg of the group owns columns vbase + j * vstep, j < VPL
-  const int vbase = tile * a.tile_w + lg * hv_col_lane(CONTIG, VPL);
-  const int vstep = hv_col_step(CONTIG, GL);
+  // lane lg of the group owns columns vcol + j * vstep, those with vok[j]
+  const int vbase = tile * a.tile_w + lg * (ADJ ? VPL : 1);
+  const int vstep = ADJ ? 1 : GL;
+  vcol = ADJ ? min(vbase, a.nvec - VPL) : vbase;
+  bool full = true;
 #pragma unroll
-  for (int j = 0; j < VPL; ++j) vok[j] = vbase + j * vstep < a.nvec;
+  for (int j = 0; j < VPL; ++j) {
+    vok[j] = ADJ ? vcol + j >= vbase : vbase + j * vstep < a.nvec;
+    full = full && vok[j];
+  }
+  // uniform: two lanes per representative, one column each, rows of two
+  // elements that start on a two-element boundary (see the gather)
+  const bool pair_rows = (VAR == kAdjacent || VAR == kDeep) && VPL == 1 && a.pad && GL == 2 && a.ld == 2 &&
+                         ((uintptr_t)a.X & (2 * sizeof(T) - 1)) == 0;
+  // uniform: a slice is DG * VPL adjacent elements
+  const bool flat = VAR == kNarrow && a.ld == VPL;
   const W lmask = (W(1) << a.b) - 1;
   const int ncand = 2 * a.nbonds;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) dot[j] = 0.0;
 
-  for (uint64_t p = slot; p < a.n_reps; p += slot_stride) {
+  for (uint64_t p = slot; p < p_end; p += slot_stride) {
     const uint64_t mp = a.meta[p];
     const int sp = (int)(mp >> 48);
     const int np_ = (int)stabf[4 * sp];
@@ -248,219 +304,300 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
 #pragma unroll
       for (int j = 0; j < VPL; ++j) acc[q][j] = 0.0;
 
-    const uint64_t e_begin = OTF ? 0 : a.row_ptr[p];
-    uint64_t e_end = OTF ? (uint64_t)ncand : a.row_ptr[p + 1];
-    // on the fly: the admissible flips of p as a bit mask where it fits 128
-    // bits, each lane of the group testing every GL-th one; e then counts
-    // admissible flips, so no lane searches for an inadmissible one
-    uint64_t adm0 = 0, adm1 = 0;
-    const bool listed = OTF && ncand <= 128;
-    if constexpr (OTF) {
-      if (listed) {
-        for (int q = lg; q < ncand; q += GL) {
-          const int bond = q >> 1;
-          const int ai = dev::digit(plab, bonds[2 * bond], a.b, lmask);
-          const int aj = dev::digit(plab, bonds[2 * bond + 1], a.b, lmask);
-          const uint64_t ok = (q & 1) ? (ai > 0 && aj < a.dloc - 1) : (ai < a.dloc - 1 && aj > 0);
-          if (q < 64)
-            adm0 |= ok << q;
-          else
-            adm1 |= ok << (q - 64);
-        }
-        for (int off = 1; off < GL; off <<= 1) {
-          adm0 |= shfl64(adm0, lane ^ off);
-          adm1 |= shfl64(adm1, lane ^ off);
-        }
-        e_end = (uint64_t)(__popcll(adm0) + __popcll(adm1));
-        // lane lg starts at the lg-th admissible flip
-        for (int q = 0; q < lg; ++q) {
-          if (adm0)
-            adm0 &= adm0 - 1;
-          else
-            adm1 &= adm1 - 1;
+    // an entry (target index, h << 32, flip id << 48, trivial target << 63)
+    auto load_entry = [&](uint64_t e) -> uint64_t {
+      if (!a.eidx) return a.entries[e];
+      const uint32_t hc = a.ehc[e];
+      return (uint64_t)a.eidx[e] | ((uint64_t)(hc & ((1u << a.hbits) - 1)) << 32) |
+             ((uint64_t)((hc & 0x7fffu) >> a.hbits) << 48) | ((uint64_t)(hc >> 15) << 63);
+    };
+    auto decode = [&](uint64_t ent) -> Flip {
+      Flip f;
+      const uint32_t idx = (uint32_t)(ent & 0xffffffffu);
+      const bool triv = ent >> 63;
+      f.c = 0.0;
+      f.off = offp * (uint64_t)a.ld;
+      f.info = 0;
+      if (idx == kInvalid) return f;
+      uint64_t row;
+      int sr;
+      if (a.pad) {
+        sr = triv ? a.triv_sid : (int)a.sid[idx];
+        row = dev::padded_row((uint32_t)a.dstride, a.rpl, a.rpline, idx);
+      } else {
+        // block rows: i * d minus the rows missing before representative i,
+        // kept per 32 representatives; the metadata word only where one of
+        // the 32 has fewer than d rows or the stabilizer is not trivial
+        const uint32_t lack = triv ? a.lack[idx >> 5] : 0x80000000u;
+        if (lack & 0x80000000u) {
+          const uint64_t m = a.meta[idx];
+          sr = (int)(m >> 48);
+          row = m & kOffMask;
+        } else {
+          sr = a.triv_sid;
+          row = (uint64_t)idx * (uint32_t)a.dstride - lack;
         }
       }
-    }
-    for (uint64_t e = e_begin; e < e_end; e += GL) {
-      // ---- one flip per lane: entry and target metadata
-      uint64_t my = kInvalid;
-      if constexpr (!OTF) {
-        if (e + lg < e_end) {
-          if (a.eidx) {
-            const uint32_t hc = a.ehc[e + lg];
-            my = (uint64_t)a.eidx[e + lg] | ((uint64_t)(hc & ((1u << a.hbits) - 1)) << 32) |
-                 ((uint64_t)((hc & 0x7fffu) >> a.hbits) << 48) | ((uint64_t)(hc >> 15) << 63);
-          } else {
-            my = a.entries[e + lg];
+      const int nr = (int)stabf[4 * sr];
+      if (nr == 0) return f;
+      int h = (int)((ent >> 32) & 0xffff);
+      const int cand = (int)((ent >> 48) & 0x7fff);
+      const int bond = cand >> 1;
+      const int ai = dev::digit(plab, bonds[2 * bond], a.b, lmask);
+      const int aj = dev::digit(plab, bonds[2 * bond + 1], a.b, lmask);
+      const double c = Jb[bond] * fac[((cand & 1) * a.dloc + ai) * a.dloc + aj] * stabf[4 * sr + 2];
+      // G x Z2: (g, F) has index |G| + g and matrix fpar * rho(g)
+      const bool flipped = h >= a.Gbase;
+      f.c = flipped ? c * a.fpar : c;
+      f.info = (uint32_t)(flipped ? h - a.Gbase : h) | ((uint32_t)sr << 16);
+      f.off = row * (uint64_t)a.ld | ((uint64_t)nr << 56) | (stabf[4 * sr + 3] != 0.0 ? Flip::kTrivial : 0) |
+              (ADJ && !a.pad && row + DG > a.rows ? Flip::kEnd : 0);
+      return f;
+    };
+    // Gather of the target's rows.  Every lane loads from an in-bounds
+    // address and rows >= n_r are zeroed afterwards (padded rows hold zeros
+    // there), so all loads of a flip are in flight together.
+    auto gather = [&](const Flip& f, T (&xv)[DG][VPL]) {
+      const T* xr = a.X + (f.off & Flip::kOff) + vcol;
+      if constexpr (!ADJ) {
+        const int nr = f.n();
+#pragma unroll
+        for (int q = 0; q < DG; ++q)
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) {
+            const bool use = vok[j] && q < nr;
+            const T val = xr[(q < nr ? q : 0) * a.ld + (vok[j] ? j * vstep : -vcol)];
+            xv[q][j] = use ? val : T(0);
+          }
+      } else if (pair_rows) {
+        // lane 0 loads rows 0 .. H-1 and lane 1 rows H .. DG-1 (H = ceil(DG / 2)),
+        // both columns of a row in one load, then each lane hands the other
+        // column to its partner: ceil(DG / 2) loads per flip instead of DG
+        constexpr int H = (DG + 1) / 2;
+        const Elems<T, 2>* x2 = reinterpret_cast<const Elems<T, 2>*>(a.X + (f.off & Flip::kOff));
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+          const Elems<T, 2> v = x2[lg ? (k + H < DG ? k + H : DG - 1) : k];
+          const T recv = pair_swap(lg ? v.v[0] : v.v[1]);
+          const T keep = lg ? v.v[1] : v.v[0];
+          xv[k][0] = lg ? recv : keep;
+          if (k + H < DG) xv[k + H][0] = lg ? keep : recv;
+        }
+      } else if (f.off & Flip::kEnd) {
+        const int nr = f.n();
+#pragma unroll
+        for (int q = 0; q < DG; ++q)
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) xv[q][j] = q < nr ? xr[q * a.ld + j] : T(0);
+      } else {
+        if (flat) {
+          const Elems<T, DG * VPL> v = *reinterpret_cast<const Elems<T, DG * VPL>*>(xr);
+#pragma unroll
+          for (int q = 0; q < DG; ++q)
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) xv[q][j] = v.v[q * VPL + j];
+        } else {
+#pragma unroll
+          for (int q = 0; q < DG; ++q) {
+            const Elems<T, VPL> v = *reinterpret_cast<const Elems<T, VPL>*>(xr + q * a.ld);
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) xv[q][j] = v.v[j];
           }
         }
+      }
+    };
+    // One flip's term: rho(h)^T (after V_r for a target with a non-trivial
+    // stabilizer) applied to c times the gathered rows, row by row of the
+    // target.
+    auto accumulate = [&](const Flip& f, T (&xv)[DG][VPL]) {
+      const double* R = rhoT + (size_t)f.h() * DG * DG;
+      if (f.off & Flip::kTrivial) {
+        // one column of rho^T ahead of the products, and no more: left alone
+        // the compiler keeps all DG x DG elements in registers
+        double r[2][DG];
+#pragma unroll
+        for (int be = 0; be < DG; ++be) r[0][be] = R[be * DG];
+#pragma unroll
+        for (int q = 0; q < DG; ++q) {
+          if (q + 1 < DG) {
+#pragma unroll
+            for (int be = 0; be < DG; ++be) r[(q + 1) & 1][be] = R[be * DG + q + 1];
+          }
+          double x[VPL];
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) x[j] = f.c * (double)xv[q][j];
+#pragma unroll
+          for (int be = 0; be < DG; ++be) {
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) acc[be][j] = fma(r[q & 1][be], x[j], acc[be][j]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       } else {
-        int cand = (int)e + lg;
-        bool ok = cand < (int)e_end;
+        if (ADJ && !a.pad) {
+          const int nr = f.n();
+#pragma unroll
+          for (int q = 1; q < DG; ++q)
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) xv[q][j] = q < nr ? xv[q][j] : T(0);
+        }
+        // The matrices are re-read for every vector (offset by the runtime
+        // zero a.zero) so the compiler cannot keep both d x d matrices live
+        // across the vector loop.
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) {
+          const double* Vr = Vt + (size_t)f.sr() * DG * DG + j * a.zero;
+          const double* Rj = R + j * a.zero;
+#pragma unroll
+          for (int q = 0; q < DG; ++q) {
+            double t = 0.0;
+#pragma unroll
+            for (int k = 0; k < DG; ++k) t = fma(Vr[q * DG + k], (double)xv[k][j], t);
+            t *= f.c;
+#pragma unroll
+            for (int be = 0; be < DG; ++be) acc[be][j] = fma(Rj[be * DG + q], t, acc[be][j]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+    };
+
+    constexpr int kWords = (DG * VPL * (int)sizeof(T) + 3) / 4;  // registers of one gathered slice
+    if constexpr (VAR == kNarrow) {
+      // slices in flight per lane, by their registers
+      constexpr int U = kWords <= 10 ? 4 : kWords <= 24 ? 2 : 1;
+      const uint64_t e_end = a.row_ptr[p + 1];
+      for (uint64_t e = a.row_ptr[p]; e < e_end; e += U) {
+        Flip f[U];
+        T xv[U][DG][VPL];
+        uint64_t ent[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) ent[u] = load_entry(min(e + u, e_end - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) f[u] = decode(e + u < e_end ? ent[u] : (uint64_t)kInvalid);
+#pragma unroll
+        for (int u = 0; u < U; ++u) gather(f[u], xv[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (f[u].n()) accumulate(f[u], xv[u]);
+      }
+    } else {
+      uint64_t e_begin = OTF ? 0 : a.row_ptr[p];
+      uint64_t e_end = OTF ? (uint64_t)ncand : a.row_ptr[p + 1];
+      // on the fly: the admissible flips of p as a bit mask where it fits 128
+      // bits, each lane of the group testing every GL-th one; e then counts
+      // admissible flips, so no lane searches for an inadmissible one
+      uint64_t adm0 = 0, adm1 = 0;
+      const bool listed = OTF && ncand <= 128;
+      if constexpr (OTF) {
         if (listed) {
-          cand = adm0 ? __builtin_ctzll(adm0) : adm1 ? 64 + __builtin_ctzll(adm1) : 0;
-          for (int q = 0; q < GL; ++q) {
+          for (int q = lg; q < ncand; q += GL) {
+            const int bond = q >> 1;
+            const int ai = dev::digit(plab, bonds[2 * bond], a.b, lmask);
+            const int aj = dev::digit(plab, bonds[2 * bond + 1], a.b, lmask);
+            const uint64_t ok = (q & 1) ? (ai > 0 && aj < a.dloc - 1) : (ai < a.dloc - 1 && aj > 0);
+            if (q < 64)
+              adm0 |= ok << q;
+            else
+              adm1 |= ok << (q - 64);
+          }
+          for (int off = 1; off < GL; off <<= 1) {
+            adm0 |= shfl64(adm0, lane ^ off);
+            adm1 |= shfl64(adm1, lane ^ off);
+          }
+          e_end = (uint64_t)(__popcll(adm0) + __popcll(adm1));
+          // lane lg starts at the lg-th admissible flip
+          for (int q = 0; q < lg; ++q) {
             if (adm0)
               adm0 &= adm0 - 1;
             else
               adm1 &= adm1 - 1;
           }
         }
-        W x = plab;
-        if (ok) {
-          const int bond = cand >> 1;
-          const int i = bonds[2 * bond], j = bonds[2 * bond + 1];
-          const int ai = dev::digit(plab, i, a.b, lmask), aj = dev::digit(plab, j, a.b, lmask);
-          ok = (cand & 1) ? (ai > 0 && aj < a.dloc - 1) : (ai < a.dloc - 1 && aj > 0);
-          const W ui = W(1) << (i * a.b), uj = W(1) << (j * a.b);
-          if (ok) x = (cand & 1) ? (plab - ui + uj) : (plab + ui - uj);
-        }
-        W r;
-        int h, ties;
-        dev::orbit_min<W, GW, kPlain<NCH, GW>>(x, ok, osearch, r, h, ties);
-        uint64_t idx = 0;
-        if (ok && lookup_rep<W>(r, a.N, a.b, a.dloc, a.A_tot, ocnt, a.cnt_stride, a.D_M, a.ranks, idx))
-          my = idx | ((uint64_t)h << 32) | ((uint64_t)cand << 48) | ((uint64_t)(ties == 1) << 63);
       }
-      const uint32_t myidx = (uint32_t)(my & 0xffffffffu);
-      uint64_t mm = 0;
-      if (myidx != kInvalid) {
-        if (a.pad) {
-          const uint64_t sr = (my >> 63) ? (uint64_t)a.triv_sid : (uint64_t)a.sid[myidx];
-          mm = dev::padded_row((uint32_t)a.dstride, a.rpl, a.rpline, myidx) | (sr << 48);
-        } else {
-          mm = a.meta[myidx];
-        }
+      uint64_t next = kInvalid;
+      if constexpr (!OTF) {
+        if (e_begin + lg < e_end) next = load_entry(e_begin + lg);
       }
-      const int cnt = (int)min((uint64_t)GL, e_end - e);
-
-      // Branch-free gathers: every lane loads from an in-bounds address
-      // (row offr and column 0 stand in for rows >= n_r and columns >= nvec)
-      // and a select zeroes those values, so all loads of a flip are in
-      // flight together instead of each waiting inside its own branch.
-      auto gather = [&](uint64_t offr, int nr, T (&xv)[DG][VPL]) {
-        if (pair_rows) {
-          // two lanes, one column each, rows of two elements: lane 0 loads
-          // rows 0 .. H-1 and lane 1 rows H .. DG-1 (H = ceil(DG / 2)), both
-          // columns of a row in one load, then each lane hands the other
-          // column to its partner.  ceil(DG / 2) loads per flip instead of DG.
-          constexpr int H = (DG + 1) / 2;
-          const RowPair<T>* xr = reinterpret_cast<const RowPair<T>*>(a.X) + offr;
-#pragma unroll
-          for (int k = 0; k < H; ++k) {
-            const RowPair<T> v = xr[lg ? (k + H < DG ? k + H : DG - 1) : k];
-            const T recv = pair_swap(lg ? v.c0 : v.c1);
-            const T keep = lg ? v.c1 : v.c0;
-            xv[k][0] = lg ? recv : keep;
-            if (k + H < DG) xv[k + H][0] = lg ? keep : recv;
-          }
-        } else if (dense) {
-          // padded rows with d_Gamma == DG and every column in range: rows
-          // k >= n_r of a target are stored zeros, so no clamp or select
-          const T* xr = a.X + offr * (uint64_t)a.ld + vbase;
-#pragma unroll
-          for (int q = 0; q < DG; ++q)
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) xv[q][j] = xr[q * a.ld + j * vstep];
+      for (uint64_t e = e_begin; e < e_end; e += GL) {
+        // ---- one flip per lane, decoded by that lane; the next chunk's
+        // entries are loaded while this one's slices are gathered
+        uint64_t my = next;
+        if constexpr (!OTF) {
+          next = kInvalid;
+          if (e + GL + lg < e_end) next = load_entry(e + GL + lg);
         } else {
-#pragma unroll
-          for (int q = 0; q < DG; ++q)
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-              const bool use = vok[j] && q < nr;
-              const uint64_t at = (offr + (q < nr ? q : 0)) * a.ld + (vok[j] ? vbase + j * vstep : 0);
-              const T val = a.X[at];
-              xv[q][j] = use ? val : T(0);
-            }
-        }
-      };
-      // one flip's term: its coefficient times rho(h)^T (after V_r for a
-      // target with a non-trivial stabilizer) applied to the gathered rows
-      auto accumulate = [&](uint64_t ent, int sr, const T (&xv)[DG][VPL]) {
-        int h = (int)((ent >> 32) & 0xffff);
-        const int cand = (int)((ent >> 48) & 0x7fff);
-        const int bond = cand >> 1;
-        const int ai = dev::digit(plab, bonds[2 * bond], a.b, lmask);
-        const int aj = dev::digit(plab, bonds[2 * bond + 1], a.b, lmask);
-        double c = Jb[bond] * fac[((cand & 1) * a.dloc + ai) * a.dloc + aj] * stabf[4 * sr + 2];
-        // G x Z2: (g, F) has index |G| + g and matrix fpar * rho(g)
-        const bool flipped = h >= a.Gbase;
-        h = flipped ? h - a.Gbase : h;
-        c = flipped ? c * a.fpar : c;
-        const double* R = rhoT + (size_t)h * DG * DG;
-        if (stabf[4 * sr + 3] != 0.0) {
-#pragma unroll
-          for (int be = 0; be < DG; ++be) {
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-              double s = 0.0;
-#pragma unroll
-              for (int q = 0; q < DG; ++q) s += R[be * DG + q] * (double)xv[q][j];
-              acc[be][j] += c * s;
+          my = kInvalid;
+          int cand = (int)e + lg;
+          bool ok = cand < (int)e_end;
+          if (listed) {
+            cand = adm0 ? __builtin_ctzll(adm0) : adm1 ? 64 + __builtin_ctzll(adm1) : 0;
+            for (int q = 0; q < GL; ++q) {
+              if (adm0)
+                adm0 &= adm0 - 1;
+              else
+                adm1 &= adm1 - 1;
             }
           }
-        } else {
-          // Non-trivial stabilizer: expand with V_r first.  The matrices are
-          // re-read from LDS for every vector (offset by the runtime zero
-          // a.zero) so the compiler cannot keep both d x d matrices live
-          // across the vector loop.
-#pragma unroll
-          for (int j = 0; j < VPL; ++j) {
-            const double* Vr = Vt + (size_t)sr * DG * DG + j * a.zero;
-            const double* Rj = R + j * a.zero;
-            double t[DG];
-#pragma unroll
-            for (int q = 0; q < DG; ++q) {
-              double s = 0.0;
-#pragma unroll
-              for (int k = 0; k < DG; ++k) s += Vr[q * DG + k] * (double)xv[k][j];
-              t[q] = s;
-            }
-#pragma unroll
-            for (int be = 0; be < DG; ++be) {
-              double s = 0.0;
-#pragma unroll
-              for (int q = 0; q < DG; ++q) s += Rj[be * DG + q] * t[q];
-              acc[be][j] += c * s;
-            }
+          W x = plab;
+          if (ok) {
+            const int bond = cand >> 1;
+            const int i = bonds[2 * bond], j = bonds[2 * bond + 1];
+            const int ai = dev::digit(plab, i, a.b, lmask), aj = dev::digit(plab, j, a.b, lmask);
+            ok = (cand & 1) ? (ai > 0 && aj < a.dloc - 1) : (ai < a.dloc - 1 && aj > 0);
+            const W ui = W(1) << (i * a.b), uj = W(1) << (j * a.b);
+            if (ok) x = (cand & 1) ? (plab - ui + uj) : (plab + ui - uj);
           }
+          W r;
+          int h, ties;
+          dev::orbit_min<W, GW, kPlain<NCH, GW>>(x, ok, osearch, r, h, ties);
+          uint64_t idx = 0;
+          if (ok && lookup_rep<W>(r, a.N, a.b, a.dloc, a.A_tot, ocnt, a.cnt_stride, a.D_M, a.ranks, idx))
+            my = idx | ((uint64_t)h << 32) | ((uint64_t)cand << 48) | ((uint64_t)(ties == 1) << 63);
         }
-      };
-      // With several vectors per lane and a flip's rows in at most 12
-      // elements and 48 bytes the gathers of two flips are in flight
-      // together, which doubles the random requests a lane group keeps
-      // outstanding; the terms are still added in flip order, so the result
-      // is the same bit for bit.  (Measured: the ten-block icosidodecahedron
-      // job 1.48 s against 1.53 s; with more registers per flip, one vector
-      // per lane or FP64 rows of 3 x 3 doubles it was slower, and FP16 rows
-      // of 15 elements took 4.0 ms per icosidodecahedron H_g launch against
-      // 3.5 ms with one flip at a time.)
-      constexpr bool kTwo = VPL > 1 && DG * VPL <= 12 && DG * VPL * sizeof(T) <= 48;
+        const Flip mine = decode(my);
+        const int cnt = (int)min((uint64_t)GL, e_end - e);
+        auto flip_of = [&](int jj) -> Flip {
+          Flip f;
+          f.c = __longlong_as_double((long long)shfl64((uint64_t)__double_as_longlong(mine.c), gbase + jj));
+          f.off = shfl64(mine.off, gbase + jj);
+          f.info = (uint32_t)__shfl((int)mine.info, gbase + jj);
+          return f;
+        };
+        // (a flip without a term gathers the output representative's own
+        // rows: a branch around the loads made the launch 25% slower)
+        if constexpr (VAR == kDeep) {
+          // a ring of slices, each gathered kRing - 1 flips before its term
+          // is added (terms in flip order)
+          constexpr int kRing = kWords <= 16 ? 4 : 3;
+          Flip f[kRing];
+          T xv[kRing][DG][VPL];
+#pragma unroll
+          for (int k = 0; k < kRing - 1; ++k)
+            if (k < cnt) {
+              f[k] = flip_of(k);
+              gather(f[k], xv[k]);
+            }
 #pragma unroll 1
-      for (int jj = 0; jj < cnt; jj += (kTwo ? 2 : 1)) {
-        const uint64_t ent0 = shfl64(my, gbase + jj);
-        const uint64_t mr0 = shfl64(mm, gbase + jj);
-        const int sr0 = (int)(mr0 >> 48);
-        const int nr0 = (int)stabf[4 * sr0];
-        const bool ok0 = (uint32_t)(ent0 & 0xffffffffu) != kInvalid && nr0 != 0;
-        if constexpr (kTwo) {
-          const int j1 = jj + 1 < cnt ? jj + 1 : jj;
-          const uint64_t ent1 = shfl64(my, gbase + j1);
-          const uint64_t mr1 = shfl64(mm, gbase + j1);
-          const int sr1 = (int)(mr1 >> 48);
-          const int nr1 = (int)stabf[4 * sr1];
-          const bool ok1 = jj + 1 < cnt && (uint32_t)(ent1 & 0xffffffffu) != kInvalid && nr1 != 0;
-          // a skipped flip gathers the output representative's own rows
-          T xv0[DG][VPL], xv1[DG][VPL];
-          gather(ok0 ? (mr0 & kOffMask) : offp, ok0 ? nr0 : 1, xv0);
-          gather(ok1 ? (mr1 & kOffMask) : offp, ok1 ? nr1 : 1, xv1);
-          if (ok0) accumulate(ent0, sr0, xv0);
-          if (ok1) accumulate(ent1, sr1, xv1);
+          for (int jj = 0; jj < cnt; jj += kRing) {
+#pragma unroll
+            for (int k = 0; k < kRing; ++k) {
+              const int ahead = jj + k + kRing - 1, at = (k + kRing - 1) % kRing;
+              if (ahead < cnt) {
+                f[at] = flip_of(ahead);
+                gather(f[at], xv[at]);
+              }
+              if (jj + k < cnt && f[k].n()) accumulate(f[k], xv[k]);
+            }
+          }
         } else {
-          if (!ok0) continue;
-          T xv[DG][VPL];
-          gather(mr0 & kOffMask, nr0, xv);
-          accumulate(ent0, sr0, xv);
+#pragma unroll 1
+          for (int jj = 0; jj < cnt; ++jj) {
+            const Flip f = flip_of(jj);
+            T xv[DG][VPL];
+            gather(f, xv);
+            if (f.n()) accumulate(f, xv);
+          }
         }
       }
     }
@@ -468,10 +605,23 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
     const double sqL = stabf[4 * sp + 1];
     const bool ptriv = stabf[4 * sp + 3] != 0.0;
     const double* Vp = Vt + (size_t)sp * DG * DG;
-    const double ed = a.ediag[p];
+    const double ed = a.ediag[p] - a.eshift;
 #pragma unroll
     for (int k = 0; k < DG; ++k) {
       if (k >= np_) break;
+      __builtin_amdgcn_sched_barrier(0);
+      const uint64_t at = (offp + k) * (uint64_t)a.ld + vcol;
+      T xk[VPL], yk[VPL];
+      if (ADJ) {
+        const Elems<T, VPL> v = *reinterpret_cast<const Elems<T, VPL>*>(a.X + at);
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) xk[j] = v.v[j];
+        if (EPI) {
+          const Elems<T, VPL> w = *reinterpret_cast<const Elems<T, VPL>*>(a.Y + at);
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) yk[j] = w.v[j];
+        }
+      }
 #pragma unroll
       for (int j = 0; j < VPL; ++j) {
         double y;
@@ -480,33 +630,45 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
         } else {
           double s = 0.0;
 #pragma unroll
-          for (int be = 0; be < DG; ++be) s += Vp[be * DG + k] * acc[be][j];
+          for (int be = 0; be < DG; ++be) s = fma(Vp[be * DG + k], acc[be][j], s);
           y = s;
         }
         y *= sqL;
-        if (vok[j]) {
-          const int v = vbase + j * vstep;
-          const uint64_t at = (offp + k) * a.ld + v;
-          const double xv = (double)a.X[at];
-          const double hx = y + (ed - a.eshift) * xv;
+        if (ADJ || vok[j]) {
+          const int v = vcol + j * vstep;
+          const double xv = (double)(ADJ ? xk[j] : a.X[at + j * vstep]);
+          const double hx = fma(ed, xv, y);
           if (!EPI) {
-            a.Y[at] = (T)hx;
+            yk[j] = (T)hx;
           } else {
             const double sj = a.scal[2 * v], bsj = a.scal[2 * v + 1];
-            const T ws = (T)(sj * hx - bsj * (double)a.Y[at]);
-            a.Y[at] = ws;
+            const T ws = (T)(sj * hx - bsj * (double)(ADJ ? yk[j] : a.Y[at + j * vstep]));
+            yk[j] = ws;
             dot[j] += xv * (double)ws;
           }
+          if (!ADJ) a.Y[at + j * vstep] = yk[j];
+        }
+      }
+      if (ADJ) {
+        if (full) {
+          Elems<T, VPL> w;
+#pragma unroll
+          for (int j = 0; j < VPL; ++j) w.v[j] = yk[j];
+          *reinterpret_cast<Elems<T, VPL>*>(a.Y + at) = w;
+        } else {
+#pragma unroll
+          for (int j = 0; j < VPL; ++j)
+            if (vok[j]) a.Y[at + j] = yk[j];
         }
       }
     }
   }
 }
 
-template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB, bool SLDS, bool CONTIG = false,
+template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB, bool SLDS, int VAR = kGeneral,
           bool VG = false>
 __global__ void __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(DG * VPL <= FTLM_HV_FLOOR_WIDTH ? FTLM_HV_WAVES_PER_EU : 1)))
+__attribute__((amdgpu_waves_per_eu(VAR == kDeep ? 1 : hv_waves(DG * VPL))))
 k_hv(HvArgs<T> a) {
   using W = word_t<NCH>;
   extern __shared__ uint64_t smem_raw[];
@@ -535,44 +697,47 @@ k_hv(HvArgs<T> a) {
     osearch.zf_ = a.zf != 0;
     osearch.full = (W)a.full;
   }
-  const double* rhoT = a.rhoT;
-  const double* Vt = a.V;
-  const double* stabf = a.stabf;
-  const double* Jb = a.J;
-  const double* fac = a.fac;
-  const int32_t* bonds = a.bonds;
-  if constexpr (SLDS) {
-    rhoT = stage<double>(a.rhoT, (uint32_t)a.G * DG * DG, sm + a.o_rho);
-    if constexpr (!VG) Vt = stage<double>(a.V, (uint32_t)a.n_stab * DG * DG, sm + a.o_V);
-    stabf = stage<double>(a.stabf, (uint32_t)a.n_stab * 4, sm + a.o_stab);
-    Jb = stage<double>(a.J, (uint32_t)a.nbonds, sm + a.o_J);
-    fac = stage<double>(a.fac, (uint32_t)(2 * a.dloc * a.dloc), sm + a.o_fac);
-    bonds = stage<int32_t>(a.bonds, (uint32_t)(2 * a.nbonds), sm + a.o_bonds);
-  }
+  if constexpr (SLDS) stage_small(a.small, a.small_bytes, (uint8_t*)sm + a.o_small);
   if constexpr (SLDS || GW > 0) __syncthreads();
-
-  const HvTabs tb{rhoT, Vt, stabf, Jb, fac, bonds};
+  const uint8_t* const tabs = SLDS ? (const uint8_t*)sm + a.o_small : a.small;
+  const HvTabs tb = small_tabs(a, tabs, VG ? a.small : tabs);
   const int lane = threadIdx.x & 63;
   const int GL = a.GL;
   const int slots_per_wave = 64 >> a.log2GL;
   const int waves = blockDim.x >> 6;
-  const uint64_t slot = ((uint64_t)blockIdx.x * waves + (threadIdx.x >> 6)) * slots_per_wave + (lane >> a.log2GL);
-  const uint64_t slot_stride = (uint64_t)gridDim.x * waves * slots_per_wave;
+  // Workgroups run round-robin over the 8 XCDs.  Each XCD takes sweeps of
+  // adjacent representatives (sweep_w workgroups, each striding over them
+  // sweep_k times), because close representatives have many targets in common
+  // and each XCD has its own L2: L2 misses of the d = 5, 24-column launch
+  // 1.58e8 -> 1.38e8.  Sweeps of 64 workgroups measured best (16: 3% slower;
+  // one eighth of the sector per XCD: 10% slower, its workgroups' fronts are
+  // too far apart).
+  const uint32_t per_wg = (uint32_t)(waves * slots_per_wave);
+  const uint32_t on_xcd = blockIdx.x >> 3;
+  const uint32_t sweep = (on_xcd / a.sweep_w) * 8 + (blockIdx.x & 7);
+  const uint64_t sweep_reps = (uint64_t)a.sweep_k * a.sweep_w * per_wg;
+  const uint64_t slot = sweep * sweep_reps + (on_xcd % a.sweep_w) * per_wg +
+                        (threadIdx.x >> 6) * slots_per_wave + (lane >> a.log2GL);
+  const uint64_t slot_stride = (uint64_t)a.sweep_w * per_wg;
+  const uint64_t p_end = min(a.n_reps, (sweep + 1) * sweep_reps);
   double dot[VPL];
   bool vok[VPL];
-  hv_pass<T, DG, VPL, GW, NCH, CONTIG>(a, tb, osearch, ocnt, (int)blockIdx.y, (int)gridDim.y, slot, slot_stride, dot, vok);
+  int vcol;
+  hv_pass<T, DG, VPL, GW, NCH, VAR>(a, tb, osearch, ocnt, (int)blockIdx.y, slot, slot_stride, p_end, dot, vok,
+                                         vcol);
   if (EPI) {
     __shared__ double red[kThreads];
     // one vector slot j at a time: lanes with equal lg hold the same column
+    const int vstep = VAR == kGeneral ? GL : 1;
 #pragma unroll
     for (int j = 0; j < VPL; ++j) {
-      red[threadIdx.x] = vok[j] ? dot[j] : 0.0;
+      red[threadIdx.x] = dot[j];
       __syncthreads();
       if ((int)threadIdx.x < GL) {
         double s = 0.0;
         for (int q = 0; q < kThreads / GL; ++q) s += red[q * GL + threadIdx.x];
-        const int vv = blockIdx.y * a.tile_w + (int)threadIdx.x * hv_col_lane(CONTIG, VPL) + j * hv_col_step(CONTIG, GL);
-        if (vv < a.nvec) a.partials[(size_t)blockIdx.x * a.nvec + vv] = s;
+        // (threads below GL are the first group's lanes, their columns the sums')
+        if (vok[j]) a.partials[(size_t)blockIdx.x * a.nvec + vcol + j * vstep] = s;
       }
       __syncthreads();
     }
@@ -581,20 +746,34 @@ k_hv(HvArgs<T> a) {
 
 template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB>
 void launch_k(const HvArgs<T>& a, const LaunchCfg& c, hipStream_t st) {
-  // adjacent-column kernels for the dimension buckets 1-6 (a dense launch of
-  // bucket 8 or 12 needs d_Gamma exactly 8 or 12; it takes the default layout)
+  // adjacent-column kernels for the dimension buckets 1-6 (buckets 8 and 12
+  // take the general ones)
   if constexpr (GW == 0 && DG <= 6) {
-    if (c.slds && c.contig) {
-      if (c.vg)
-        hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
-      else
-        hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, true>), c.grid, dim3(kThreads), c.shm, st, a);
+    if (c.slds && c.var != kGeneral) {
+      auto go = [&](auto var) {
+        constexpr int V = decltype(var)::value;
+        if (c.vg)
+          hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, V, true>), c.grid, dim3(kThreads), c.shm, st, a);
+        else
+          hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, V>), c.grid, dim3(kThreads), c.shm, st, a);
+      };
+      if constexpr (VPL <= 4) {
+        if (c.var == kDeep) {
+          go(std::integral_constant<int, kDeep>{});
+          return;
+        }
+        if (c.var == kNarrow) {
+          go(std::integral_constant<int, kNarrow>{});
+          return;
+        }
+      }
+      go(std::integral_constant<int, kAdjacent>{});
       return;
     }
   }
   if constexpr (GW == 0) {
     if (c.slds && c.vg) {
-      hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, false, true>), c.grid, dim3(kThreads), c.shm, st, a);
+      hipLaunchKernelGGL((k_hv<T, DG, VPL, GW, NCH, LDS_TAB, true, kGeneral, true>), c.grid, dim3(kThreads), c.shm, st, a);
       return;
     }
   }

@@ -70,12 +70,11 @@ struct Sector {
   uint64_t n_entries = 0;
   DevBuf<int32_t> d_bonds;
   DevBuf<double> d_J;
-  DevBuf<double> d_fac;         // [2][d][d] ladder products (J = 1)
+  std::vector<double> fac;      // [2][d][d] ladder products (J = 1)
   int64_t device_bytes() const {
     return (int64_t)(d_tab.bytes() + d_cnt.bytes() + d_ranks.bytes() +
                      d_reps.bytes() + d_stab_id.bytes() + d_ediag.bytes() + d_row_ptr.bytes() +
-                     d_entries.bytes() + d_eidx.bytes() + d_ehc.bytes() + d_bonds.bytes() + d_J.bytes() +
-                     d_fac.bytes());
+                     d_entries.bytes() + d_eidx.bytes() + d_ehc.bytes() + d_bonds.bytes() + d_J.bytes());
   }
 };
 
@@ -96,11 +95,19 @@ struct Block {
   std::vector<uint8_t> trivial; // V = identity and n = d
   // device
   DevBuf<uint64_t> d_meta;      // per representative: offset | stab_id << 48
-  DevBuf<double> d_rhoT64;      // [g][beta][gamma] = rho(g)[gamma][beta]
-  DevBuf<double> d_V64;         // [s][gamma][k]
-  DevBuf<double> d_stabf64;     // [s]: {n, sqrtL, 1/sqrtL, trivial}
+  // block rows: i d_Gamma - offset(i) at i = 32 w, top bit set when one of the
+  // 32 representatives has fewer than d_Gamma rows (or the count needs the bit)
+  DevBuf<uint32_t> d_lack;
+  // the H.V's small tables in one array, in the order and at the 16-byte
+  // aligned offsets they have in LDS, so a workgroup stages them in one copy:
+  // rho^T [g][beta][gamma] = rho(g)[gamma][beta] at 0, per stabilizer {n,
+  // sqrtL, 1/sqrtL, trivial}, J, ladder products, bonds, V [s][gamma][k] last
+  // (kernels without V in LDS stage what is before it)
+  DevBuf<uint8_t> d_small;
+  uint32_t o_stab = 0, o_J = 0, o_fac = 0, o_bonds = 0, o_V = 0, small_bytes = 0;
+  const double* stabf() const { return (const double*)(d_small.p + o_stab); }
   int64_t device_bytes() const {
-    return (int64_t)(d_meta.bytes() + d_rhoT64.bytes() + d_V64.bytes() + d_stabf64.bytes()) +
+    return (int64_t)(d_meta.bytes() + d_lack.bytes() + d_small.bytes()) +
            sec->device_bytes();
   }
 };
@@ -246,7 +253,8 @@ bool wg_supported(const Block& b, int R, int storage);
 uint64_t wg_rounds(uint64_t n_reps, int R);
 // automatic engine choice: blocks whose sector needs at most this many
 // representative rounds per lane group and step go to the fused kernel
-constexpr uint64_t kWgAutoMaxRounds = 8;
+// (dodecahedron campaign, R = 24: 8 -> 99 ms, 12 -> 84, 18 -> 87, 24 -> 87 ms)
+constexpr uint64_t kWgAutoMaxRounds = 12;
 // chains one fused job can hold (one column per lane group slot)
 constexpr int kWgMaxChains = 32;
 struct WgTask {

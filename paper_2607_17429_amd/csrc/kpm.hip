@@ -188,7 +188,7 @@ void kpm_typed(const Block& b, int R, int M, uint64_t seed, int dist, double cen
   const uint64_t D = vec_rows(b, vl);
   const uint64_t* meta = vl.pad ? b.d_meta.p : nullptr;
   const dev::PadMap pm = pad_map(b, vl);
-  const double* stabf = b.d_stabf64.p;
+  const double* stabf = b.stabf();
   const int TB = R * (256 / R);
   const unsigned nb = groups_for(D, TB / R);
   const int dtype = sizeof(T) == 8 ? FTLM_F64 : FTLM_F32;

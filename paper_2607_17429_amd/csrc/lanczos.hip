@@ -234,7 +234,7 @@ void enqueue_begin_typed(LanczosRun& L, hipStream_t st) {
   if (L.target == 0) return;
   // start vectors: norm of the FP64 draw, then the stored, normalised q_0 and its norm
   const uint64_t* meta = L.vl.pad ? L.block->d_meta.p : nullptr;
-  const double* stabf = L.block->d_stabf64.p;
+  const double* stabf = L.block->stabf();
   const dev::PadMap pm = pad_map(*L.block, L.vl);
   hipLaunchKernelGGL((k_start<T>), dim3(L.nb_vec), dim3(L.TB), 0, st, L.keys.p, L.dist, D, R, (const double*)nullptr,
                      q0, L.partials.p, meta, stabf, pm);

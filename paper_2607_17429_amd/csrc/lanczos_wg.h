@@ -38,6 +38,7 @@ struct WgJob {
   uint64_t D;
   int R, steps, target, dist;
   double sigma;         // storage scale of the stored vectors (1 for FP32 / FP64)
+  int dgp;              // irrep dimension bucket
   int lds_vec;          // 1: q0, q1 live in dynamic LDS at byte offset o_q (q0 and q1 unused)
   uint32_t o_q;
 };
@@ -72,23 +73,30 @@ __device__ __forceinline__ void wg_chain_sum(double x, int R, int RB, double* re
   __syncthreads();
 }
 
-template <typename T, int DG, int VPL, int NCH>
-__global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* __restrict__ jobs) {
-  constexpr int NT = kWgThreads<DG>;
-  using W = word_t<NCH>;
-  extern __shared__ uint64_t smem_raw[];
-  char* sm = (char*)smem_raw;
-  __shared__ double red[NT];
-  __shared__ double scal[2 * kWgMaxR];
-  __shared__ double csum[kWgMaxR];
-  __shared__ WgChain ch[kWgMaxR];
+struct WgShared {
+  double red[512];
+  double scal[2 * kWgMaxR];
+  double csum[kWgMaxR];
+  WgChain ch[kWgMaxR];
+};
 
-  const WgJob<T>& J = jobs[blockIdx.x];
+// LV: the two Lanczos vectors are in LDS (decided per job on the host), known
+// at compile time so their accesses are LDS instructions.
+template <typename T, int DG, int VPL, bool LV>
+__device__ __forceinline__ void wg_run(const WgJob<T>& J, char* sm, WgShared& sh) {
+  constexpr int NT = kWgThreads<DG>;
+  // adjacent columns for the buckets that equal d_Gamma (R >= VPL always)
+  constexpr int kVar = DG <= 6 ? kDeep : kGeneral;
+  constexpr int NCH = 16;  // 64-bit label words serve every label
+  using W = word_t<NCH>;
+  double* const red = sh.red;
+  double* const scal = sh.scal;
+  double* const csum = sh.csum;
+  WgChain* const ch = sh.ch;
+
   HvArgs<T> a = J.a;
-  // the two Lanczos vectors: in LDS when they fit (the H.V gathers and the
-  // update then never leave the CU), otherwise in device memory
-  T* const q0 = J.lds_vec ? (T*)(sm + J.o_q) : J.q0;
-  T* const q1 = J.lds_vec ? q0 + J.D * (uint64_t)J.R : J.q1;
+  T* const q0 = LV ? (T*)(sm + J.o_q) : J.q0;
+  T* const q1 = LV ? q0 + J.D * (uint64_t)J.R : J.q1;
   double* const alpha = J.alpha;
   double* const beta = J.beta;
   const uint64_t D = J.D;
@@ -96,12 +104,8 @@ __global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* _
   const double sigma = J.sigma;
   const int t = threadIdx.x;
 
-  const HvTabs tb{stage<double>(a.rhoT, (uint32_t)a.G * DG * DG, sm + a.o_rho),
-                  stage<double>(a.V, (uint32_t)a.n_stab * DG * DG, sm + a.o_V),
-                  stage<double>(a.stabf, (uint32_t)a.n_stab * 4, sm + a.o_stab),
-                  stage<double>(a.J, (uint32_t)a.nbonds, sm + a.o_J),
-                  stage<double>(a.fac, (uint32_t)(2 * a.dloc * a.dloc), sm + a.o_fac),
-                  stage<int32_t>(a.bonds, (uint32_t)(2 * a.nbonds), sm + a.o_bonds)};
+  stage_small(a.small, a.small_bytes, (uint8_t*)sm + a.o_small);
+  const HvTabs tb = small_tabs(a, (const uint8_t*)sm + a.o_small, (const uint8_t*)sm + a.o_small);
   const dev::Orbit<W, 1, false> none{};  // flips come from the entry table
   for (int i = t; i < R * steps; i += NT) {
     alpha[i] = 0.0;
@@ -157,14 +161,15 @@ __global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* _
     a.Y = qp;
     double dot[VPL];
     bool vok[VPL];
-    hv_pass<T, DG, VPL, 0, NCH>(a, tb, none, nullptr, 0, 1, slot, slot_stride, dot, vok);
+    int vcol;
+    hv_pass<T, DG, VPL, 0, NCH, kVar>(a, tb, none, nullptr, 0, slot, slot_stride, a.n_reps, dot, vok, vcol);
     // column sums of q_j . w: lanes with equal (lane mod GL) hold the same column
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
       red[t] = vok[k] ? dot[k] : 0.0;
       __syncthreads();
       wg_col_sum(red, GL, NT / GL);
-      if (t < GL && t + k * GL < R) csum[t + k * GL] = red[t];
+      if (t < GL && vok[k]) csum[vcol + k * (kVar == kGeneral ? GL : 1)] = red[t];
       __syncthreads();
     }
     if (t < R) {
@@ -216,41 +221,53 @@ __global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg(const WgJob<T>* _
   if (t < R) J.nsteps[t] = ch[t].n;
 }
 
-// One launch: grid = one workgroup per job, all jobs of one kernel shape.
-template <int DG>
-void wg_launch(int dtype, int vpl, bool wide, const void* jobs, int njobs, size_t shm, hipStream_t st);
-
 template <typename T, int DG, int VPL>
-void wg_launch_t(bool wide, const void* jobs, int njobs, size_t shm, hipStream_t st) {
-  if (wide)
-    hipLaunchKernelGGL((k_lanczos_wg<T, DG, VPL, 16>), dim3(njobs), dim3(kWgThreads<DG>), shm, st,
-                       (const WgJob<T>*)jobs);
+__device__ __forceinline__ void wg_job(const WgJob<T>& J, char* sm, WgShared& sh) {
+  if (J.lds_vec)
+    wg_run<T, DG, VPL, true>(J, sm, sh);
   else
-    hipLaunchKernelGGL((k_lanczos_wg<T, DG, VPL, 8>), dim3(njobs), dim3(kWgThreads<DG>), shm, st,
-                       (const WgJob<T>*)jobs);
+    wg_run<T, DG, VPL, false>(J, sm, sh);
 }
 
-template <typename T, int DG>
-void wg_launch_v(int vpl, bool wide, const void* jobs, int njobs, size_t shm, hipStream_t st) {
-  switch (vpl) {
-    case 1: wg_launch_t<T, DG, 1>(wide, jobs, njobs, shm, st); break;
-    case 2: wg_launch_t<T, DG, 2>(wide, jobs, njobs, shm, st); break;
-    case 3: wg_launch_t<T, DG, 3>(wide, jobs, njobs, shm, st); break;
-    case 4: wg_launch_t<T, DG, 4>(wide, jobs, njobs, shm, st); break;
-    default: fail(FTLM_ERR_INVALID_ARG, "fused Lanczos: unsupported vectors per lane");
+// The jobs of dimension buckets up to 6 share one launch, whatever their
+// dimension (uniform per workgroup): a launch per bucket ran one after the
+// other, each waiting for its longest job, with most of the device idle.
+template <typename T, int VPL>
+__global__ void __launch_bounds__(kWgThreads<1>) k_lanczos_wg(const WgJob<T>* __restrict__ jobs) {
+  extern __shared__ uint64_t smem_raw[];
+  __shared__ WgShared sh;
+  const WgJob<T>& J = jobs[blockIdx.x];
+  switch (J.dgp) {
+    case 1: wg_job<T, 1, VPL>(J, (char*)smem_raw, sh); break;
+    case 2: wg_job<T, 2, VPL>(J, (char*)smem_raw, sh); break;
+    case 3: wg_job<T, 3, VPL>(J, (char*)smem_raw, sh); break;
+    case 4: wg_job<T, 4, VPL>(J, (char*)smem_raw, sh); break;
+    case 5: wg_job<T, 5, VPL>(J, (char*)smem_raw, sh); break;
+    case 6: wg_job<T, 6, VPL>(J, (char*)smem_raw, sh); break;
   }
 }
 
-#define FTLM_WG_INSTANTIATE(DGV)                                                                          \
-  template <>                                                                                            \
-  void wg_launch<DGV>(int dtype, int vpl, bool wide, const void* jobs, int njobs, size_t shm,            \
-                      hipStream_t st) {                                                                  \
-    if (dtype == FTLM_F64)                                                                               \
-      wg_launch_v<double, DGV>(vpl, wide, jobs, njobs, shm, st);                                         \
-    else if (dtype == FTLM_F32)                                                                          \
-      wg_launch_v<float, DGV>(vpl, wide, jobs, njobs, shm, st);                                          \
-    else                                                                                                 \
-      fail(FTLM_ERR_INVALID_ARG, "fused Lanczos: storage must be FTLM_F64 or FTLM_F32");                 \
+template <typename T, int DG, int VPL>
+__global__ void __launch_bounds__(kWgThreads<DG>) k_lanczos_wg_wide(const WgJob<T>* __restrict__ jobs) {
+  extern __shared__ uint64_t smem_raw[];
+  __shared__ WgShared sh;
+  wg_run<T, DG, VPL, false>(jobs[blockIdx.x], (char*)smem_raw, sh);
+}
+
+// One launch: grid = one workgroup per job; wide = 0 (buckets 1 to 6), 8 or 12.
+template <typename T, int VPL>
+void wg_launch(int wide, const void* jobs, int njobs, size_t shm, hipStream_t st);
+
+#define FTLM_WG_INSTANTIATE(T, V)                                                                                  \
+  template <>                                                                                                     \
+  void wg_launch<T, V>(int wide, const void* jobs, int njobs, size_t shm, hipStream_t st) {                       \
+    const WgJob<T>* j = (const WgJob<T>*)jobs;                                                                    \
+    if (wide == 0)                                                                                                \
+      hipLaunchKernelGGL((k_lanczos_wg<T, V>), dim3(njobs), dim3(kWgThreads<1>), shm, st, j);                     \
+    else if (wide == 8)                                                                                           \
+      hipLaunchKernelGGL((k_lanczos_wg_wide<T, 8, V>), dim3(njobs), dim3(kWgThreads<8>), shm, st, j);             \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_lanczos_wg_wide<T, 12, V>), dim3(njobs), dim3(kWgThreads<12>), shm, st, j);           \
   }
 
 }  // namespace hvk

@@ -1,7 +1,7 @@
 // Host side of the fused small-block Lanczos kernel (lanczos_wg.h): which
 // blocks it can run, one device arena per batch of block jobs, jobs grouped by
-// kernel shape (storage type, irrep dimension bucket, vectors per lane, label
-// width) with one launch per group, and the results copied back per job.
+// kernel (storage type, vectors per lane, dimension buckets up to 6 together)
+// with one launch per group, and the results copied back per job.
 #include <cstring>
 #include <map>
 #include <tuple>
@@ -14,12 +14,19 @@ using namespace hvk;
 
 namespace {
 
-// lanes per representative: 4 for up to 4 chains (flip entries of a chunk are
-// fetched together), else 8 with up to 4 vectors per lane
-int wg_lanes(int R) { return R <= 4 ? 4 : 8; }
+// lanes per representative: at least 4 for up to 4 chains (flip entries of a
+// chunk are decoded together) and as many more, up to 32, as the workgroup's
+// 512 threads give every representative of the sector; else 8 with up to 4
+// vectors per lane
+int wg_lanes(uint64_t n_reps, int R) {
+  if (R > 4) return 8;
+  int gl = 4;
+  while (gl < 32 && n_reps * (uint64_t)(2 * gl) <= 512) gl *= 2;
+  return gl;
+}
 
 // dynamic LDS a job may use for its tables and, when they fit, its two
-// vectors (the kernel's static LDS takes another ~4.6 KiB of the 64 KiB)
+// vectors (the kernel's static LDS takes another 6.5 KiB of the 64 KiB)
 constexpr size_t kWgLdsBytes = 56 * 1024;
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -27,25 +34,28 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 size_t elem_bytes(int storage) { return storage == FTLM_F64 ? 8 : 4; }
 
 struct Shape {
-  int dtype, dgp, vpl;
-  bool wide;
-  bool operator<(const Shape& o) const {
-    return std::tie(dtype, dgp, vpl, wide) < std::tie(o.dtype, o.dgp, o.vpl, o.wide);
-  }
+  int dtype, wide, vpl;  // wide: 0 for dimension buckets up to 6, else the bucket
+  bool operator<(const Shape& o) const { return std::tie(dtype, wide, vpl) < std::tie(o.dtype, o.wide, o.vpl); }
 };
 
-void launch_shape(const Shape& sh, const void* jobs, int n, size_t shm, hipStream_t st) {
-  switch (sh.dgp) {
-    case 1: wg_launch<1>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 2: wg_launch<2>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 3: wg_launch<3>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 4: wg_launch<4>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 5: wg_launch<5>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 6: wg_launch<6>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 8: wg_launch<8>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    case 12: wg_launch<12>(sh.dtype, sh.vpl, sh.wide, jobs, n, shm, st); break;
-    default: fail(FTLM_ERR_DIM_GT_12, "irrep dimension above 12");
+template <typename T>
+void launch_typed(const Shape& sh, const void* jobs, int n, size_t shm, hipStream_t st) {
+  switch (sh.vpl) {
+    case 1: wg_launch<T, 1>(sh.wide, jobs, n, shm, st); break;
+    case 2: wg_launch<T, 2>(sh.wide, jobs, n, shm, st); break;
+    case 3: wg_launch<T, 3>(sh.wide, jobs, n, shm, st); break;
+    case 4: wg_launch<T, 4>(sh.wide, jobs, n, shm, st); break;
+    default: fail(FTLM_ERR_INVALID_ARG, "fused Lanczos: unsupported vectors per lane");
   }
+}
+
+void launch_shape(const Shape& sh, const void* jobs, int n, size_t shm, hipStream_t st) {
+  if (sh.dtype == FTLM_F64)
+    launch_typed<double>(sh, jobs, n, shm, st);
+  else if (sh.dtype == FTLM_F32)
+    launch_typed<float>(sh, jobs, n, shm, st);
+  else
+    fail(FTLM_ERR_INVALID_ARG, "fused Lanczos: storage must be FTLM_F64 or FTLM_F32");
 }
 
 }  // namespace
@@ -59,13 +69,13 @@ bool wg_supported(const Block& b, int R, int storage) {
   if (irrep_dim_bucket(b.dg) < 0) return false;
   LaunchCfg c{};
   HvArgs<double> a{};
-  hv_setup(b, R, R, wg_lanes(R), VecLayout{}, nullptr, c, a);
+  hv_setup(b, R, R, wg_lanes(b.sec->n_reps, R), VecLayout{}, nullptr, c, a);
   return c.slds && !c.vg && a.tile_w >= R && c.vpl <= 4;
 }
 
 uint64_t wg_rounds(uint64_t n_reps, int R) {
   // workgroups of 512 threads (irrep dimensions up to 6)
-  const uint64_t slots = (uint64_t)kWgThreads<1> / (uint64_t)wg_lanes(R);
+  const uint64_t slots = (uint64_t)kWgThreads<1> / (uint64_t)(R <= 4 ? 4 : 8);
   return (n_reps + slots - 1) / slots;
 }
 
@@ -86,10 +96,10 @@ WgBatch::WgBatch(std::vector<WgTask> t, hipStream_t st_) : tasks(std::move(t)), 
     const WgTask& k = tasks[i];
     const Block& b = *k.block;
     if (k.storage == FTLM_F64)
-      hv_setup(b, k.R, k.R, wg_lanes(k.R), VecLayout{}, nullptr, cfg[i], a64[i]);
+      hv_setup(b, k.R, k.R, wg_lanes(b.sec->n_reps, k.R), VecLayout{}, nullptr, cfg[i], a64[i]);
     else
-      hv_setup(b, k.R, k.R, wg_lanes(k.R), VecLayout{}, nullptr, cfg[i], a32[i]);
-    shape[i] = Shape{k.storage, b.dgp, cfg[i].vpl, b.sec->wide};
+      hv_setup(b, k.R, k.R, wg_lanes(b.sec->n_reps, k.R), VecLayout{}, nullptr, cfg[i], a32[i]);
+    shape[i] = Shape{k.storage, b.dgp <= 6 ? 0 : b.dgp, cfg[i].vpl};
     groups[shape[i]].push_back(i);
   }
   // arena: [job arrays][keys] (uploaded) [alpha][beta][n] (downloaded) [q0 q1 per job]
@@ -128,7 +138,7 @@ WgBatch::WgBatch(std::vector<WgTask> t, hipStream_t st_) : tasks(std::move(t)), 
     const size_t oq = (cfg[i].shm + 15) & ~size_t(15);
     shm[i] = cfg[i].shm;
     oq0[i] = oq1[i] = 0;
-    if (oq + 2 * qb <= kWgLdsBytes) {
+    if (tasks[i].block->dgp <= 6 && oq + 2 * qb <= kWgLdsBytes) {
       in_lds[i] = 1;
       lds_q[i] = (uint32_t)oq;
       shm[i] = oq + 2 * qb;
@@ -165,6 +175,7 @@ WgBatch::WgBatch(std::vector<WgTask> t, hipStream_t st_) : tasks(std::move(t)), 
         job.target = (int)std::min<uint64_t>((uint64_t)k.steps, b.D);
         job.dist = k.dist;
         job.sigma = 1.0;
+        job.dgp = b.dgp;
         job.lds_vec = in_lds[i];
         job.o_q = lds_q[i];
         if (job.lds_vec) job.q0 = job.q1 = nullptr;

@@ -578,7 +578,8 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
   const int G_ = G->order;
   const size_t wbytes = s.wide ? 8 : 4;
   std::vector<uint8_t> tab_host;                 // host copies of tables in flight to the device
-  std::vector<double> fac(2 * s.d * s.d);
+  std::vector<double>& fac = s.fac;
+  fac.assign(2 * s.d * s.d, 0.0);
   {
     const int max_plain = (int)std::max<size_t>(1, 16384 / ((size_t)s.nch * 16 * wbytes));
     const Factorization fz = factor_group(*G, max_plain);
@@ -643,7 +644,6 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
         fac[(1 * s.d + ai) * s.d + aj] = 0.5 * std::sqrt(std::max(0.0, ss - mi * (mi - 1))) *
                                          std::sqrt(std::max(0.0, ss - mj * (mj + 1)));
       }
-    s.d_fac.upload_async(fac, st);
   }
   SecArgs a{};
   orbit_args(s, a);
