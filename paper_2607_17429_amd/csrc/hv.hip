@@ -43,25 +43,38 @@ int vpl_bucket(int need, bool otf) {
 // Whether the adjacent-column kernels can run the block (hv_setup's rule)
 bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && b.dg == b.dgp && b.dgp <= 6; }
 
-// Default lanes per output representative.  A sector of up to 4,096
-// representatives takes 32 whatever the vectors: its few waves wait for one
-// another's flips, not for lanes, and 32 lanes decode a whole row of flips at
-// once (dodecahedron H_g at M = 0, 1,648 representatives, FP64: 24 vectors 19
-// us against 40 with 8 lanes, one vector 19 against 36 us with one lane).
-// Above (measured on MI355X on the s = 1/2 icosidodecahedron at M = 0): up to 4 vectors one lane that holds them all
-// where the sector has enough representatives to fill the device that way
-// (2 FP32 vectors, d = 5: 0.66 against 0.70 ms with two lanes), one lane per
-// vector otherwise; above, about 3 vectors per lane, or 6 in FP16 (whose rows
-// are then whole 4-byte words; 24 vectors, d = 3: 1.40 against 1.67 ms) where
-// half as many lanes still fill the device (a sector of a few thousand
-// representatives took 42 us with 6 per lane, 24 us with 3).
+// Default lanes per output representative (ms on MI355X, s = 1/2
+// icosidodecahedron at M = 0 unless stated):
+//   one lane that holds every column for rows of up to 8 bytes (one FP64
+//   column, d = 5: 0.74; two FP32: 0.66 against 0.70 with two lanes); wider
+//   rows cost it more registers than the exchange it saves (two FP64: 1.01
+//   against 0.85; four: 1.74 against 1.07);
+//   up to 4 vectors one lane each;
+//   above, 3 vectors per lane, 4 in FP32 and FP16 where that halves the lanes
+//   (13 FP32 vectors, d = 5: 1.77 against 1.95; 7: 1.28 against 1.14, so not
+//   below 8 lanes), and 6 in FP16, whose rows are then whole 4-byte words (24
+//   vectors, d = 3: 1.40 against 1.67), where the sector is large;
+//   more lanes, up to 32, where the sector's representatives leave the device
+//   idle otherwise: few waves wait for one another's flips, and many lanes
+//   decode a row's flips at once (dodecahedron H_g at M = 0, 1,648
+//   representatives, FP64: 24 vectors 19 us against 40 with 8 lanes, one
+//   vector 19 against 36 us; 17,238 representatives, one vector: 30 us with 4
+//   lanes, 44 with one).
 int default_lanes(const Block& b, int nvec, int dtype) {
-  if (b.sec->hv_mode != FTLM_HV_ONTHEFLY && adjacent_ok(b) && nvec <= 32 && b.sec->n_reps * 32 <= kDeepLanes) return 32;
   if (b.sec->hv_mode == FTLM_HV_ONTHEFLY)
     return nvec <= 4 ? pow2_at_least(nvec) : std::min(16, pow2_at_least((nvec + 3) / 4));
-  if (nvec <= 4) return adjacent_ok(b) && b.sec->n_reps >= (1u << 17) ? 1 : pow2_at_least(nvec);
-  if (dtype == FTLM_F16 && adjacent_ok(b) && b.sec->n_reps >= (1u << 16)) return pow2_at_least((nvec + 5) / 6);
-  return pow2_at_least((nvec + 2) / 3);
+  const int elem = dtype == FTLM_F64 ? 8 : dtype == FTLM_F32 ? 4 : 2;
+  int gl = nvec <= 4 ? pow2_at_least(nvec) : pow2_at_least((nvec + 2) / 3);
+  if (!adjacent_ok(b)) return gl;
+  if (nvec * elem <= 8)
+    gl = 1;
+  else if (elem == 2 && nvec > 4 && b.sec->n_reps >= (1u << 16))
+    gl = pow2_at_least((nvec + 5) / 6);
+  else if (elem < 8 && gl >= 8 && gl * 2 >= nvec)
+    gl /= 2;
+  if (nvec <= 32)
+    while (gl < 32 && b.sec->n_reps * (uint64_t)(2 * gl) <= kDeepLanes) gl *= 2;
+  return gl;
 }
 
 // Lanes per output representative (GL) and vectors per lane (VPL) for gl lanes
