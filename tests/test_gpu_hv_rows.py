@@ -50,3 +50,25 @@ def test_block_rows(name, two_s, two_M, gi, dtype):
         Ye, _ = LB.apply_H_ex(Xt, torch.zeros_like(out)[:, :nvec], layout=P.LAYOUT_BLOCK, scale=sb, dots=dots)
         p = Xt.double() * Ye.double()
         assert torch.all((dots - p.sum(0)).abs() <= 1e-12 * p.abs().sum(0) + 1e-300)
+
+
+@pytest.mark.parametrize("name,two_M,irrep", [("ring20_C", 0, 3), ("ring20_C", 2, 10), ("ring20_C", 4, 1), ("icosahedron", 12, 0),
+                                              ("dodecahedron", 0, 9), ("ring20_C", 16, 2)])
+def test_row_offsets(name, two_M, irrep):
+    """Row offsets built by one workgroup (up to 8,192 representatives) and by
+    the scan (above), sectors of 1 to 9,252: the exported offsets are the
+    prefix sums of n_Gamma, and a product that finds its targets through them
+    equals the padded-row product, whose targets need none, bit for bit."""
+    from synth import clusters
+    cl = clusters.get(name)
+    B = P.Block(P.Sector(cl, P.Group(cl.N, cl.gens), two_M, two_s=1), irrep)
+    ex = B.export()
+    n = ex["n_gamma"].astype(np.int64)
+    live = n > 0
+    assert np.array_equal(ex["offsets"].astype(np.int64)[live], (np.cumsum(n) - n)[live]) and n.sum() == B.D
+    rows = np.concatenate([i * B.d_gamma + np.arange(n[i]) for i in np.nonzero(live)[0]])
+    X = torch.from_numpy(np.random.default_rng(2).standard_normal((B.D, 3))).cuda()
+    Xp = torch.zeros((B.D_pad, 3), dtype=torch.float64, device="cuda")
+    Xp[torch.from_numpy(rows).cuda()] = X
+    Yp, _ = B.apply_H_ex(Xp, layout=P.LAYOUT_PADDED)
+    assert torch.equal(B.apply_H(X), Yp[torch.from_numpy(rows).cuda()])
