@@ -45,10 +45,14 @@ bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && 
 
 // Default lanes per output representative (ms on MI355X, s = 1/2
 // icosidodecahedron at M = 0 unless stated):
-//   one lane that holds every column for rows of up to 8 bytes (one FP64
-//   column, d = 5: 0.74; two FP32: 0.66 against 0.70 with two lanes); wider
-//   rows cost it more registers than the exchange it saves (two FP64: 1.01
-//   against 0.85; four: 1.74 against 1.07);
+//   one lane that holds every column for rows of up to 8 bytes (two FP32,
+//   d = 5: 0.67 against 0.69 with two lanes; one FP64, d = 3: 0.50 against
+//   0.58); wider rows cost it more registers than the exchange it saves (two
+//   FP64: 1.01 against 0.85; four: 1.74 against 1.07).  From d = 5 on two
+//   lanes that share the decoding are the better for one column (one FP64,
+//   d = 5: 0.65 against 0.74, padded rows 0.57 against 0.75) and, in padded
+//   rows, for two, whose row pairs they split (0.58 against 0.63; the s = 3/2
+//   dodecahedron, 7.2e8 representatives: 520 against 633);
 //   up to 4 vectors one lane each;
 //   above, 3 vectors per lane, 4 in FP32 and FP16 where that halves the lanes
 //   (13 FP32 vectors, d = 5: 1.77 against 1.95; 7: 1.28 against 1.14, so not
@@ -60,14 +64,14 @@ bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && 
 //   representatives, FP64: 24 vectors 19 us against 40 with 8 lanes, one
 //   vector 19 against 36 us; 17,238 representatives, one vector: 30 us with 4
 //   lanes, 44 with one).
-int default_lanes(const Block& b, int nvec, int dtype) {
+int default_lanes(const Block& b, int nvec, int dtype, bool pad) {
   if (b.sec->hv_mode == FTLM_HV_ONTHEFLY)
     return nvec <= 4 ? pow2_at_least(nvec) : std::min(16, pow2_at_least((nvec + 3) / 4));
   const int elem = dtype == FTLM_F64 ? 8 : dtype == FTLM_F32 ? 4 : 2;
   int gl = nvec <= 4 ? pow2_at_least(nvec) : pow2_at_least((nvec + 2) / 3);
   if (!adjacent_ok(b)) return gl;
   if (nvec * elem <= 8)
-    gl = 1;
+    gl = b.dg >= 5 && (pad || nvec == 1) ? 2 : 1;
   else if (elem == 2 && nvec > 4 && b.sec->n_reps >= (1u << 16))
     gl = pow2_at_least((nvec + 5) / 6);
   else if (elem < 8 && gl >= 8 && gl * 2 >= nvec)
@@ -150,7 +154,7 @@ TuneKey tune_key(const Block& b, int nvec, int dtype, const VecLayout& vl, bool 
 
 int tuned_gl(const Block& b, int nvec, int dtype, const VecLayout& vl, bool epi) {
   const int gl = tune_lookup(tune_key(b, nvec, dtype, vl, epi));
-  return gl > 0 ? gl : default_lanes(b, nvec, dtype);
+  return gl > 0 ? gl : default_lanes(b, nvec, dtype, vl.pad);
 }
 
 // Column sums of a (ng x nvec) array of per-workgroup partials, one workgroup
