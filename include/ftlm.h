@@ -336,9 +336,9 @@ int ftlm_apply_H_ex(ftlm_block* b, const void* X, void* Y, int32_t nvec, int64_t
  * device memory: work captured into a HIP graph, tight serving loops,
  * harnesses that forbid allocation.  Same arguments, results bit for bit
  * equal to ftlm_apply_H_ex.  Its one scratch buffer (the per-workgroup FP64
- * partial sums behind scale/dots) is a static device array of 4 MiB per GPU
- * (8192 x 64 doubles), held until the process ends; INVALID_ARG when a call
- * would need more (nvec x workgroups above that).  The first call on a
+ * partial sums behind scale/dots) is a static device array of 5 MiB per GPU,
+ * held until the process ends; INVALID_ARG when nvec x workgroups (before the
+ * launch rounds them to whole sweeps) is above 8192 x 64.  The first call on a
  * device looks up the array's device address (hipGetSymbolAddress): make it
  * outside stream capture.  Every call on one GPU shares that GPU's array:
  * calls that overlap in time on one GPU (several streams or host threads)

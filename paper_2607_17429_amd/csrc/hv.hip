@@ -69,7 +69,7 @@ int default_lanes(const Block& b, int nvec, int dtype, bool pad) {
     return nvec <= 4 ? pow2_at_least(nvec) : std::min(16, pow2_at_least((nvec + 3) / 4));
   const int elem = dtype == FTLM_F64 ? 8 : dtype == FTLM_F32 ? 4 : 2;
   int gl = nvec <= 4 ? pow2_at_least(nvec) : pow2_at_least((nvec + 2) / 3);
-  if (!adjacent_ok(b)) return gl;
+  if (!adjacent_ok(b) || nvec > 64) return gl;
   if (nvec * elem <= 8)
     gl = b.dg >= 5 && (pad || nvec == 1) ? 2 : 1;
   else if (elem == 2 && nvec > 4 && b.sec->n_reps >= (1u << 16))
@@ -99,7 +99,8 @@ Layout choose_layout(int nvec, bool otf, int gl) {
 }
 
 struct Sweep {
-  uint32_t w, k;  // workgroups and rounds of one sweep
+  uint32_t w, k;   // workgroups and rounds of one sweep (k = 0: workgroups in order)
+  uint64_t need;   // workgroups that give every representative a lane group
   dim3 grid;
 };
 
@@ -109,6 +110,14 @@ Sweep hv_grid(const Block& b, const Layout& L) {
   const uint64_t slots_per_block = (uint64_t)(kThreads / 64) * (64 / L.GL);
   const uint64_t need = std::max<uint64_t>(1, (b.sec->n_reps + slots_per_block - 1) / slots_per_block);
   Sweep s{};
+  s.need = need;
+  if (need <= 512) {
+    // one round of at most two workgroups a CU: nothing to sweep, and no
+    // workgroup without a representative
+    s.w = 1;
+    s.grid = dim3((unsigned)need, (unsigned)L.tiles, 1);
+    return s;
+  }
   s.k = (uint32_t)((need + TG - 1) / TG);
   const uint64_t per_xcd = ((need + s.k - 1) / s.k + 7) / 8;
   const uint64_t sweeps = (per_xcd + TW - 1) / TW;
@@ -274,6 +283,7 @@ HvExPlan plan_hv_ex(const Block& b, int nvec, int64_t ld, int dtype, const ftlm_
   const Layout L = choose_layout(nvec, otf, lanes ? lanes : tuned_gl(b, nvec, dtype, p.vl, p.epi));
   p.gl = L.GL;
   p.ng = (b.D && b.sec->n_reps) ? hv_partial_groups(b, nvec, p.gl) : 0;
+  p.ng_asked = p.ng ? (int)std::min<uint64_t>(hv_grid(b, L).need, 8192) : 0;
   if (b.D && b.sec->n_reps) {
     LaunchCfg c{};
     HvArgs<double> a{};

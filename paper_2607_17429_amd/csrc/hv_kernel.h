@@ -30,11 +30,11 @@
 // Cache, and the waves that can wait for them.  Figures (MI355X, before ->
 // after one decode per flip, four waves, adjacent columns in block rows and
 // sweeps on one XCD; icosidodecahedron M = 0, 4.02e7 flips): plain product,
-// d = 5, 24 FP32 columns 3.62 -> 2.87 ms, d = 3 3.32 -> 1.69 ms; one FP64
-// column, d = 5 1.33 -> 0.74 ms; two FP32 columns 0.91 -> 0.66 ms; 24 FP16
-// columns, d = 3 3.59 -> 1.40 ms; with the Lanczos epilogue in padded rows,
-// 24 FP32 columns, d = 5 3.34 -> 2.97 ms, d = 3 1.98 -> 1.77 ms, d = 1 0.85 ->
-// 0.79 ms.
+// d = 5, 24 FP32 columns 3.58 -> 2.77 ms, d = 3 3.32 -> 1.69 ms; one FP64
+// column, d = 5 1.33 -> 0.65 ms; two FP32 columns 0.91 -> 0.67 ms; 24 FP16
+// columns, d = 3 3.63 -> 1.41 ms; with the Lanczos epilogue in padded rows,
+// 24 FP32 columns, d = 5 3.34 -> 2.95 ms, d = 4 2.54 -> 2.24, d = 3 1.98 ->
+// 1.76 ms, d = 1 0.85 -> 0.79 ms.
 // Arithmetic is FP64; FP32 and FP16 storage round once on the store.
 //
 // Flips come from the sector's entry table (target index, h, flip id; built
@@ -101,7 +101,7 @@ struct HvArgs {
   T* Y;
   int64_t ld;
   int nvec, GL, log2GL, tile_w;
-  uint32_t sweep_w, sweep_k;  // workgroups and rounds of one sweep (see k_hv)
+  uint32_t sweep_w, sweep_k;  // workgroups and rounds of one sweep (k_hv); sweep_k = 0: workgroups in order
   int zero;  // always 0 (see the non-trivial stabilizer branch)
   // on-the-fly search (dev::Orbit; LDS: n_lds mask positions, counts, images)
   const uint64_t* mask;
@@ -198,8 +198,8 @@ __device__ __forceinline__ HvTabs small_tabs(const HvArgs<T>& a, const uint8_t* 
 }
 
 // Copies bytes (a multiple of 16) into LDS with eight 16-byte loads in flight
-// per thread: table by table with one 8-byte load at a time, the staging was
-// most of a small launch (DG = 5, 36 KB: 12 us).
+// per thread (with the kDeep ring, dodecahedron H_g at M = 0, 24 FP64 columns
+// on 8 lanes: 45 -> 40 us).
 __device__ __forceinline__ void stage_small(const uint8_t* src, uint32_t bytes, uint8_t* dst) {
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   const u4* s = (const u4*)src;
@@ -750,13 +750,16 @@ k_hv(HvArgs<T> a) {
   // one eighth of the sector per XCD: 10% slower, its workgroups' fronts are
   // too far apart).
   const uint32_t per_wg = (uint32_t)(waves * slots_per_wave);
-  const uint32_t on_xcd = blockIdx.x >> 3;
-  const uint32_t sweep = (on_xcd / a.sweep_w) * 8 + (blockIdx.x & 7);
-  const uint64_t sweep_reps = (uint64_t)a.sweep_k * a.sweep_w * per_wg;
-  const uint64_t slot = sweep * sweep_reps + (on_xcd % a.sweep_w) * per_wg +
-                        (threadIdx.x >> 6) * slots_per_wave + (lane >> a.log2GL);
-  const uint64_t slot_stride = (uint64_t)a.sweep_w * per_wg;
-  const uint64_t p_end = min(a.n_reps, (sweep + 1) * sweep_reps);
+  const uint32_t in_wg = (threadIdx.x >> 6) * slots_per_wave + (lane >> a.log2GL);
+  uint64_t slot = (uint64_t)blockIdx.x * per_wg + in_wg, slot_stride = (uint64_t)gridDim.x * per_wg, p_end = a.n_reps;
+  if (a.sweep_k) {
+    const uint32_t on_xcd = blockIdx.x >> 3;
+    const uint32_t sweep = (on_xcd / a.sweep_w) * 8 + (blockIdx.x & 7);
+    const uint64_t sweep_reps = (uint64_t)a.sweep_k * a.sweep_w * per_wg;
+    slot = sweep * sweep_reps + (on_xcd % a.sweep_w) * per_wg + in_wg;
+    slot_stride = (uint64_t)a.sweep_w * per_wg;
+    p_end = min(a.n_reps, (sweep + 1) * sweep_reps);
+  }
   double dot[VPL];
   bool vok[VPL];
   int vcol;

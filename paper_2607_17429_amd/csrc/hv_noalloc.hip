@@ -15,10 +15,12 @@ namespace ftlm {
 
 namespace {
 
-// 8192 workgroups (the H.V grid's cap) x 64 vectors of partial sums: 4 MiB
+// 8192 workgroups (the H.V grid's cap) x 64 vectors of partial sums is what a
+// call may ask for; the grid is then rounded up to whole sweeps, by at most
+// 127 workgroups and only above 512, so the array holds a quarter more: 5 MiB
 constexpr size_t kNoallocScratchDoubles = (size_t)8192 * 64;
 
-__device__ __align__(256) double scratch[kNoallocScratchDoubles];
+__device__ __align__(256) double scratch[kNoallocScratchDoubles + kNoallocScratchDoubles / 4];
 
 std::mutex g_scratch_mu;
 std::unordered_map<int, double*> g_scratch_ptr;  // device ordinal -> address of its scratch
@@ -52,8 +54,8 @@ extern "C" int ftlm_apply_H_ex_noalloc(ftlm_block* b, const void* X, void* Y, in
     const HvExPlan p = plan_hv_ex(B, nvec, ld, dtype, opts);
     double* partials = nullptr;
     if (p.epi && p.ng > 0) {
-      if ((size_t)p.ng * (size_t)nvec > kNoallocScratchDoubles)
-        fail(FTLM_ERR_INVALID_ARG, "nvec x workgroups = " + std::to_string((size_t)p.ng * nvec) +
+      if ((size_t)p.ng_asked * (size_t)nvec > kNoallocScratchDoubles)
+        fail(FTLM_ERR_INVALID_ARG, "nvec x workgroups = " + std::to_string((size_t)p.ng_asked * nvec) +
                                        " partial sums exceed the static scratch of " +
                                        std::to_string(kNoallocScratchDoubles));
       partials = device_scratch();

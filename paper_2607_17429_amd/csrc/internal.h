@@ -182,6 +182,7 @@ struct HvExPlan {
   VecLayout vl;
   bool epi = false, adjacent = false;
   int gl = 0, ng = 0;
+  int ng_asked = 0;   // workgroups before the rounding to whole sweeps, at most 8192
   uint64_t rows = 0;
 };
 HvExPlan plan_hv_ex(const Block& b, int nvec, int64_t ld, int dtype, const ftlm_hv_opts* o);
