@@ -49,15 +49,6 @@ __host__ __device__ __forceinline__ bool padded_rep_of(const PadMap& m, uint64_t
   return slot < m.rpl && i < m.n_reps;
 }
 
-// One word of the rank lookup: bit k is set when rank 64 w + k is a
-// representative, base counts the representatives before the word.  One
-// 16-byte record, because a lookup is a random access: bits and base in
-// arrays of their own cost two lines each.
-struct alignas(16) RankWord {
-  uint64_t bits;
-  uint32_t base, unused;
-};
-
 template <typename W>
 __device__ __forceinline__ int digit(W x, int k, int b, W mask) {
   return (int)((x >> (k * b)) & mask);

@@ -9,7 +9,6 @@
 #include <vector>
 
 #include "common.h"
-#include "device.h"
 #include "group.h"
 
 struct ftlm_group {
@@ -17,6 +16,18 @@ struct ftlm_group {
 };
 
 namespace ftlm {
+
+namespace dev {
+struct PadMap;
+// One word of the rank lookup: bit k is set when rank 64 w + k is a
+// representative, base counts the representatives before the word.  One
+// 16-byte record, because a lookup is a random access: bits and base in
+// arrays of their own cost two lines each.
+struct alignas(16) RankWord {
+  uint64_t bits;
+  uint32_t base, unused;
+};
+}  // namespace dev
 
 // Irreducible-representation-independent tables of one M sector.
 struct Sector {
