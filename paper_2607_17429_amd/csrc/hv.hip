@@ -17,29 +17,6 @@ namespace {
 constexpr uint32_t kSmallLdsBudget = 48 * 1024;
 constexpr uint32_t kLdsLimit = 65536 - 2048;  // dynamic LDS; 2 KiB stay for the epilogue reduction
 
-// lanes of a launch up to which a wave seldom shares its SIMD (256 CUs x 4
-// SIMDs x 64 lanes x 2): several slices in flight per group then hide what
-// other waves cannot
-constexpr uint64_t kDeepLanes = 131072;
-
-struct Layout {
-  int GL, log2GL, VPL, tile_w, tiles;
-};
-
-int pow2_at_least(int n) {
-  int p = 1;
-  while (p < n) p <<= 1;
-  return p;
-}
-
-int vpl_bucket(int need, bool otf) {
-  if (otf) return need <= 1 ? 1 : 4;
-  const int opts[] = {1, 2, 3, 4, 6, 8};
-  for (int o : opts)
-    if (o >= need) return o;
-  return 8;
-}
-
 // Whether the adjacent-column kernels can run the block (hv_setup's rule)
 bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && b.dg == b.dgp && b.dgp <= 6; }
 
@@ -79,23 +56,6 @@ int default_lanes(const Block& b, int nvec, int dtype, bool pad) {
   if (nvec <= 32)
     while (gl < 32 && b.sec->n_reps * (uint64_t)(2 * gl) <= kDeepLanes) gl *= 2;
   return gl;
-}
-
-// Lanes per output representative (GL) and vectors per lane (VPL) for gl lanes
-// (the autotuner's choice or the default).
-Layout choose_layout(int nvec, bool otf, int gl) {
-  Layout L{};
-  L.GL = std::min(64, pow2_at_least(gl));
-  L.VPL = vpl_bucket((std::min(nvec, 64 * 8) + L.GL - 1) / L.GL, otf);
-  if (L.GL * L.VPL > 64 && L.GL > 1) {
-    // keep a tile within 64 vectors
-    L.VPL = vpl_bucket(std::max(1, 64 / L.GL), otf);
-  }
-  L.log2GL = 0;
-  while ((1 << L.log2GL) < L.GL) ++L.log2GL;
-  L.tile_w = L.GL * L.VPL;
-  L.tiles = (nvec + L.tile_w - 1) / L.tile_w;
-  return L;
 }
 
 struct Sweep {
@@ -330,11 +290,7 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   c.wide = s.wide;
   c.gw = s.gw;
   c.vpl = L.VPL;
-  // adjacent columns wherever a gathered row is whole (no row of the bucket
-  // beyond d_Gamma) and every lane can own VPL columns
-  c.var = !adjacent_ok(b) || nvec < L.VPL ? kGeneral
-          : L.GL == 1 && L.tiles == 1 && L.VPL <= 4 && nvec == L.VPL ? kNarrow
-          : L.VPL <= 4 && s.n_reps * (uint64_t)L.GL * L.tiles <= kDeepLanes ? kDeep : kAdjacent;
+  c.var = hv_variant(adjacent_ok(b), nvec, L, s.n_reps);
   // small tables first priority; the orbit search's tables take what they
   // leave (up to the soft limit that keeps two workgroups on a CU), the rest
   // of them is read through the caches

@@ -56,6 +56,7 @@
 
 #include "device.h"
 #include "dispatch.h"
+#include "hv_rows.h"
 #include "internal.h"
 
 namespace ftlm {
@@ -167,13 +168,6 @@ __device__ __forceinline__ _Float16 pair_swap(_Float16 v) {
   return __builtin_bit_cast(_Float16, (uint16_t)pair_swap_u32(__builtin_bit_cast(uint16_t, v)));
 }
 
-// Row-major elements loaded as one word of N elements at the element type's
-// alignment (global loads of up to 16 bytes need no more than that).
-template <typename T, int N>
-struct __attribute__((packed, aligned(sizeof(T)))) Elems {
-  T v[N];
-};
-
 template <typename E>
 __device__ __forceinline__ const E* stage(const E* src, uint32_t count, char* dst_bytes) {
   E* dst = (E*)dst_bytes;
@@ -215,37 +209,6 @@ __device__ __forceinline__ void stage_small(const uint8_t* src, uint32_t bytes, 
   }
 }
 
-// Kernel variants (the host picks one, hv_setup):
-//   kGeneral   lane g of a group holds columns g + j * GL; every element of a
-//              gather has its own clamped address and a select.  Any launch.
-//   kAdjacent  lane g holds the adjacent columns g * VPL + j (the last lanes
-//              move back to end at column nvec - 1 and own only the columns
-//              no other lane has), so a gathered row is one wide load per
-//              lane.  Table-driven launches with d_Gamma equal to the
-//              dimension bucket and nvec >= VPL.
-//   kNarrow    kAdjacent with one lane per representative that holds every
-//              column: no exchange between lanes, several flips' slices in
-//              flight per lane, a slice of adjacent rows in 16-byte loads.
-//   kDeep      kAdjacent with several flips' slices in flight per lane group,
-//              for launches of so few waves that none waits for another.
-enum HvVariant { kGeneral = 0, kAdjacent = 1, kNarrow = 2, kDeep = 3 };
-
-// One flip as the gather and the accumulation need it, found by one lane:
-// the coefficient c_e / sqrt(L_r) (sign of a flipped element included), the
-// element offset of the target's first row, n_r, and h, stabilizer id, flags.
-struct Flip {
-  double c;
-  uint64_t off;   // element offset (56 bits) | n_r << 56; n_r = 0: no term
-  uint32_t info;  // h | stabilizer id << 16
-  static constexpr uint64_t kOff = (1ull << 56) - 1;
-  // flags above n_r (dimensions up to 12 need 4 bits)
-  static constexpr uint64_t kTrivial = 1ull << 60;  // trivial stabilizer
-  static constexpr uint64_t kEnd = 1ull << 61;      // rows beyond n_r may lie past the array
-  __device__ __forceinline__ int n() const { return (int)(off >> 56) & 15; }
-  __device__ __forceinline__ int h() const { return (int)(info & 0xffffu); }
-  __device__ __forceinline__ int sr() const { return (int)(info >> 16); }
-};
-
 // The H.V over the representatives p = slot, slot + slot_stride, ... < p_end of
 // one column tile: lane group of GL lanes per representative (see the file text).
 // dot[j] accumulates q_j . w of this lane's column vcol + j * (column step).
@@ -271,21 +234,13 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
   const int lg = VAR == kNarrow ? 0 : lane & (GL - 1);
   const int gbase = lane - lg;
   // lane lg of the group owns columns vcol + j * vstep, those with vok[j]
-  const int vbase = tile * a.tile_w + lg * (ADJ ? VPL : 1);
   const int vstep = ADJ ? 1 : GL;
-  vcol = ADJ ? min(vbase, a.nvec - VPL) : vbase;
+  vcol = lane_columns<VAR, VPL>(tile, a.tile_w, lg, GL, a.nvec, vok);
   bool full = true;
 #pragma unroll
-  for (int j = 0; j < VPL; ++j) {
-    vok[j] = ADJ ? vcol + j >= vbase : vbase + j * vstep < a.nvec;
-    full = full && vok[j];
-  }
-  // uniform: two lanes per representative, one column each, rows of two
-  // elements that start on a two-element boundary (see the gather)
-  const bool pair_rows = (VAR == kAdjacent || VAR == kDeep) && VPL == 1 && a.pad && GL == 2 && a.ld == 2 &&
-                         ((uintptr_t)a.X & (2 * sizeof(T) - 1)) == 0;
-  // uniform: a slice is DG * VPL adjacent elements
-  const bool flat = VAR == kNarrow && a.ld == VPL;
+  for (int j = 0; j < VPL; ++j) full = full && vok[j];
+  const SliceShape shape = slice_shape<VAR, VPL>(a.pad != 0, GL, lg, a.ld, a.nvec, vcol,
+                                                 ((uintptr_t)a.X & (2 * sizeof(T) - 1)) == 0);
   const W lmask = (W(1) << a.b) - 1;
   const int ncand = 2 * a.nbonds;
 #pragma unroll
@@ -316,7 +271,7 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
       const uint32_t idx = (uint32_t)(ent & 0xffffffffu);
       const bool triv = ent >> 63;
       f.c = 0.0;
-      f.off = offp * (uint64_t)a.ld;
+      f.off = flip_word<VAR, DG>(offp, 0, false, a.pad != 0, a.rows, a.ld);
       f.info = 0;
       if (idx == kInvalid) return f;
       uint64_t row;
@@ -350,61 +305,11 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
       const bool flipped = h >= a.Gbase;
       f.c = flipped ? c * a.fpar : c;
       f.info = (uint32_t)(flipped ? h - a.Gbase : h) | ((uint32_t)sr << 16);
-      f.off = row * (uint64_t)a.ld | ((uint64_t)nr << 56) | (stabf[4 * sr + 3] != 0.0 ? Flip::kTrivial : 0) |
-              (ADJ && !a.pad && row + DG > a.rows ? Flip::kEnd : 0);
+      f.off = flip_word<VAR, DG>(row, nr, stabf[4 * sr + 3] != 0.0, a.pad != 0, a.rows, a.ld);
       return f;
     };
-    // Gather of the target's rows.  Every lane loads from an in-bounds
-    // address and rows >= n_r are zeroed afterwards (padded rows hold zeros
-    // there), so all loads of a flip are in flight together.
     auto gather = [&](const Flip& f, T (&xv)[DG][VPL]) {
-      const T* xr = a.X + (f.off & Flip::kOff) + vcol;
-      if constexpr (!ADJ) {
-        const int nr = f.n();
-#pragma unroll
-        for (int q = 0; q < DG; ++q)
-#pragma unroll
-          for (int j = 0; j < VPL; ++j) {
-            const bool use = vok[j] && q < nr;
-            const T val = xr[(q < nr ? q : 0) * a.ld + (vok[j] ? j * vstep : -vcol)];
-            xv[q][j] = use ? val : T(0);
-          }
-      } else if (pair_rows) {
-        // lane 0 loads rows 0 .. H-1 and lane 1 rows H .. DG-1 (H = ceil(DG / 2)),
-        // both columns of a row in one load, then each lane hands the other
-        // column to its partner: ceil(DG / 2) loads per flip instead of DG
-        constexpr int H = (DG + 1) / 2;
-        const Elems<T, 2>* x2 = reinterpret_cast<const Elems<T, 2>*>(a.X + (f.off & Flip::kOff));
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-          const Elems<T, 2> v = x2[lg ? (k + H < DG ? k + H : DG - 1) : k];
-          const T recv = pair_swap(lg ? v.v[0] : v.v[1]);
-          const T keep = lg ? v.v[1] : v.v[0];
-          xv[k][0] = lg ? recv : keep;
-          if (k + H < DG) xv[k + H][0] = lg ? keep : recv;
-        }
-      } else if (f.off & Flip::kEnd) {
-        const int nr = f.n();
-#pragma unroll
-        for (int q = 0; q < DG; ++q)
-#pragma unroll
-          for (int j = 0; j < VPL; ++j) xv[q][j] = q < nr ? xr[q * a.ld + j] : T(0);
-      } else {
-        if (flat) {
-          const Elems<T, DG * VPL> v = *reinterpret_cast<const Elems<T, DG * VPL>*>(xr);
-#pragma unroll
-          for (int q = 0; q < DG; ++q)
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) xv[q][j] = v.v[q * VPL + j];
-        } else {
-#pragma unroll
-          for (int q = 0; q < DG; ++q) {
-            const Elems<T, VPL> v = *reinterpret_cast<const Elems<T, VPL>*>(xr + q * a.ld);
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) xv[q][j] = v.v[j];
-          }
-        }
-      }
+      gather_slice<VAR>(a.X, f, shape, vok, xv, [](T v) { return pair_swap(v); });
     };
     // One flip's term: its coefficient times rho(h)^T (after V_r for a target
     // with a non-trivial stabilizer) applied to the gathered rows.  FP64
@@ -602,7 +507,8 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
           return f;
         };
         // (a flip without a term gathers the output representative's own
-        // rows: a branch around the loads made the launch 25% slower)
+        // rows, which flip_word keeps inside the array: a branch around the
+        // loads made the launch 25% slower)
         if constexpr (VAR == kDeep) {
           // a ring of slices, each gathered kRing - 1 flips before its term
           // is added (terms in flip order)
