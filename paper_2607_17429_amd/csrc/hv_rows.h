@@ -120,7 +120,7 @@ __host__ __device__ __forceinline__ uint64_t flip_word(uint64_t row, int nr, boo
 struct SliceShape {
   int64_t ld;
   int vcol, vstep, lg;
-  bool pair;  // two lanes per representative, one column each, rows of two elements on a two-element boundary
+  bool pair;  // two lanes per representative, one of the two columns each, rows of two elements on a two-element boundary
   bool flat;  // a slice is DG * VPL adjacent elements
 };
 
@@ -128,7 +128,8 @@ template <int VAR, int VPL>
 __host__ __device__ __forceinline__ SliceShape slice_shape(bool pad, int GL, int lg, int64_t ld, int nvec, int vcol,
                                                            bool pair_aligned) {
   return SliceShape{ld, vcol, VAR == kGeneral ? GL : 1, lg,
-                    (VAR == kAdjacent || VAR == kDeep) && VPL == 1 && pad && GL == 2 && ld == 2 && pair_aligned,
+                    (VAR == kAdjacent || VAR == kDeep) && VPL == 1 && pad && GL == 2 && nvec == 2 && ld == 2 &&
+                        pair_aligned,
                     VAR == kNarrow && ld == VPL};
 }
 

@@ -62,7 +62,7 @@ struct Rows {
 
 template <int VAR, int DG, int VPL>
 void run(const Case& c, const Rows& r, int nvec, int64_t ld, const Layout& L) {
-  const int64_t size = (int64_t)r.rows * ld;
+  const int64_t size = (int64_t)(r.rows - 1) * ld + nvec;  // the smallest array a caller may pass
   ++variants[VAR];
   auto check = [&](uint64_t first, int nr, const char* what, size_t i) {
     Flip f;
