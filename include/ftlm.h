@@ -351,9 +351,11 @@ int ftlm_apply_H_ex_noalloc(ftlm_block* b, const void* X, void* Y, int32_t nvec,
  * representative 1..64, vectors per lane) for nvec columns of dtype on this
  * block, on stream, first for the launch ftlm_run and ftlm_kpm make on this
  * block (its row layout, with the Lanczos epilogue), then for the plain
- * launch of ftlm_apply_H (block rows), and keeps the fastest of each in a
- * process-wide cache keyed by (N, 2s, |G|, irrep dimension, nvec, dtype, H.V
- * mode, row layout, epilogue); later calls with that key use it.  Outputs
+ * launch of ftlm_apply_H (block rows), and keeps the fastest of each (the
+ * default layout, which is always timed too, unless another is faster by more
+ * than 3%) in a process-wide cache keyed by (N, 2s, |G|, irrep dimension,
+ * nvec, dtype, H.V mode, row layout, epilogue); later calls with that key use
+ * it.  Outputs
  * (may be NULL) describe the first: the chosen lanes per representative and
  * its time per launch in ms; up to 8 (lanes, ms) pairs in tried/tried_ms
  * with their count in n_tried.  Allocates two rows x nvec scratch arrays for

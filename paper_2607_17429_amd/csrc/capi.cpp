@@ -186,11 +186,9 @@ int ftlm_block_autotune(ftlm_block* b, int32_t nvec, int32_t dtype, void* stream
     // the launch of ftlm_run and ftlm_kpm (their row layout, Lanczos epilogue),
     // whose times are reported, then the plain launch of ftlm_apply_H
     const int64_t elem = dtype == FTLM_F64 ? 8 : dtype == FTLM_F32 ? 4 : 2;
-    auto res = autotune_hv(B, nvec, dtype, (hipStream_t)stream, 5, run_layout(B, nvec * elem), true);
-    (void)autotune_hv(B, nvec, dtype, (hipStream_t)stream, 5, VecLayout{}, false);
     int bi = -1;
-    for (size_t i = 0; i < res.size(); ++i)
-      if (bi < 0 || res[i].second < res[bi].second) bi = (int)i;
+    auto res = autotune_hv(B, nvec, dtype, (hipStream_t)stream, 5, run_layout(B, nvec * elem), true, &bi);
+    (void)autotune_hv(B, nvec, dtype, (hipStream_t)stream, 5, VecLayout{}, false);
     if (best_lanes) *best_lanes = bi >= 0 ? res[bi].first : 0;
     if (best_ms) *best_ms = bi >= 0 ? res[bi].second : 0.0;
     const int n = (int)std::min<size_t>(res.size(), 8);

@@ -204,10 +204,12 @@ void apply_hv_ex(const Block& b, const void* X, void* Y, int nvec, int64_t ld, i
 // representative, zeros beyond n_Gamma): the block's lanczos_layout, or for
 // FTLM_LAYOUT_AUTO blocks of at least 2^20 rows that pad by at most 2%.
 bool padded_vectors(const Block& b);
-// Times every lane layout for (nvec, dtype) on this block, caches the fastest
-// process-wide and returns (lanes per representative, ms per launch) pairs.
+// Times every lane layout for (nvec, dtype) on this block, the default among
+// them, caches the fastest process-wide (the default unless another is faster
+// by more than 3%) and returns (lanes per representative, ms per launch) pairs;
+// *chosen is the index of the cached one (-1: none).
 std::vector<std::pair<int, double>> autotune_hv(const Block& b, int nvec, int dtype, hipStream_t st, int reps,
-                                                const VecLayout& vl, bool epi);
+                                                const VecLayout& vl, bool epi, int* chosen = nullptr);
 int irrep_dim_bucket(int d);
 // gcnArchName of the current device
 std::string device_arch();
