@@ -354,8 +354,8 @@ int ftlm_apply_H_ex_noalloc(ftlm_block* b, const void* X, void* Y, int32_t nvec,
  * launch of ftlm_apply_H (block rows), and keeps the fastest of each (the
  * default layout, which is always timed too, unless another is faster by more
  * than 3%) in a process-wide cache keyed by (N, 2s, |G|, irrep dimension,
- * nvec, dtype, H.V mode, row layout, epilogue); later calls with that key use
- * it.  Outputs
+ * nvec, dtype, H.V mode, row layout, epilogue, size class of the sector);
+ * later calls with that key use it.  Outputs
  * (may be NULL) describe the first: the chosen lanes per representative and
  * its time per launch in ms; up to 8 (lanes, ms) pairs in tried/tried_ms
  * with their count in n_tried.  Allocates two rows x nvec scratch arrays for
@@ -365,7 +365,10 @@ int ftlm_block_autotune(ftlm_block* b, int32_t nvec, int32_t dtype, void* stream
 
 /* The autotuner's choices outlive the process through a text file (one line
  * per choice: architecture, cluster hash, sizes, kernel bucket, vectors,
- * storage, mode, layout, epilogue, lanes).  Every key carries the device
+ * storage, mode, layout, epilogue, lanes, kernel generation, size class).
+ * Lines of another kernel generation, or without the last two fields, are
+ * taken in and saved again, but their lanes, timed on other kernels, are not
+ * used.  Every key carries the device
  * architecture (ftlm_device_arch, e.g. "gfx950:sramecc+:xnack-") and a hash
  * of the cluster (sizes, bonds, couplings, group elements, spin flip), so a
  * choice is used only for the hardware and cluster it was timed on.

@@ -104,6 +104,15 @@ std::string current_arch() {
   return names[dev] = std::string(prop.gcnArchName);
 }
 
+// Size class of a sector for the tuned lanes, with default_lanes' thresholds:
+// sectors of one class have the same default for every vector count, so lanes
+// timed on one of them do not replace another class's.
+int size_class(uint64_t n_reps) {
+  int c = 0;
+  for (uint64_t gl = 32; gl > 1 && n_reps * gl > kDeepLanes; gl /= 2) ++c;
+  return c;
+}
+
 TuneKey tune_key(const Block& b, int nvec, int dtype, const VecLayout& vl, bool epi) {
   const Sector& s = *b.sec;
   TuneKey k;
@@ -118,6 +127,8 @@ TuneKey tune_key(const Block& b, int nvec, int dtype, const VecLayout& vl, bool 
   k.mode = s.hv_mode;
   k.pad = vl.kind();
   k.epi = epi ? 1 : 0;
+  k.kernels = kTuneKernels;
+  k.size = size_class(s.n_reps);
   return k;
 }
 

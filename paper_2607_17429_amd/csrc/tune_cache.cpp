@@ -1,6 +1,7 @@
 // Autotuner cache (tune_cache.h): a mutex-guarded map in the process, and a
-// text file of "arch cluster N two_s G dgp nvec dtype mode pad epi lanes"
-// lines so that a tuned layout survives the process.  Host only.
+// text file of "arch cluster N two_s G dgp nvec dtype mode pad epi lanes kernels
+// size" lines (without the last two: an entry of kernels before the first
+// generation) so that a tuned layout survives the process.  Host only.
 #include "tune_cache.h"
 
 #include <cstdio>
@@ -20,8 +21,9 @@ std::map<TuneKey, int> g_tune;
 }  // namespace
 
 bool TuneKey::operator<(const TuneKey& o) const {
-  return std::tie(arch, cluster, N, two_s, G, dgp, nvec, dtype, mode, pad, epi) <
-         std::tie(o.arch, o.cluster, o.N, o.two_s, o.G, o.dgp, o.nvec, o.dtype, o.mode, o.pad, o.epi);
+  return std::tie(arch, cluster, N, two_s, G, dgp, nvec, dtype, mode, pad, epi, kernels, size) <
+         std::tie(o.arch, o.cluster, o.N, o.two_s, o.G, o.dgp, o.nvec, o.dtype, o.mode, o.pad, o.epi, o.kernels,
+                  o.size);
 }
 
 uint64_t fnv1a(const void* p, size_t n, uint64_t h) {
@@ -59,7 +61,9 @@ int tune_save(const char* path, const char* arch) {
       const TuneKey& k = kv.first;
       if (arch && k.arch != arch) continue;
       os << k.arch << ' ' << k.cluster << ' ' << k.N << ' ' << k.two_s << ' ' << k.G << ' ' << k.dgp << ' '
-         << k.nvec << ' ' << k.dtype << ' ' << k.mode << ' ' << k.pad << ' ' << k.epi << ' ' << kv.second << '\n';
+         << k.nvec << ' ' << k.dtype << ' ' << k.mode << ' ' << k.pad << ' ' << k.epi << ' ' << kv.second;
+      if (k.kernels) os << ' ' << k.kernels << ' ' << k.size;
+      os << '\n';
       ++n;
     }
   }
@@ -88,6 +92,11 @@ int tune_load(const char* path, const char* arch) {
       fail(FTLM_ERR_INVALID_ARG, std::string(path) + ":" + std::to_string(lineno) + ": malformed autotuner entry");
     if (lanes < 1 || lanes > 64 || (lanes & (lanes - 1)))
       fail(FTLM_ERR_INVALID_ARG, std::string(path) + ":" + std::to_string(lineno) + ": lanes must be a power of two <= 64");
+    int kernels = 0, size = 0;
+    if (is >> kernels >> size) {
+      k.kernels = kernels;
+      k.size = size;
+    }
     if (arch && k.arch != arch) continue;
     got[k] = lanes;
     ++n;
