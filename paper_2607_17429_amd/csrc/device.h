@@ -13,6 +13,7 @@
 #include <cstdint>
 
 #include "ftlm.h"
+#include "rank_word.h"
 
 namespace ftlm {
 namespace dev {
@@ -48,6 +49,8 @@ __host__ __device__ __forceinline__ bool padded_rep_of(const PadMap& m, uint64_t
   i = g * m.rpl + slot;
   return slot < m.rpl && i < m.n_reps;
 }
+
+__device__ __forceinline__ uint64_t rank_bits(const RankWord& w) { return (uint64_t)w.hi << 32 | w.lo; }
 
 template <typename W>
 __device__ __forceinline__ int digit(W x, int k, int b, W mask) {

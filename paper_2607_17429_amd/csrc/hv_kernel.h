@@ -143,8 +143,9 @@ __device__ __forceinline__ bool lookup_rep(W r, int N, int b, int d, int A, cons
   if (rk >= D_M) return false;
   const dev::RankWord w = ranks[rk >> 6];
   const int k = (int)(rk & 63);
-  idx = w.base + (uint64_t)__popcll(w.bits & ((1ull << k) - 1));
-  return (w.bits >> k) & 1;
+  const uint64_t bits = dev::rank_bits(w);
+  idx = w.base + (uint64_t)__popcll(bits & ((1ull << k) - 1));
+  return (bits >> k) & 1;
 }
 
 __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {

@@ -10,6 +10,7 @@
 
 #include "common.h"
 #include "group.h"
+#include "rank_word.h"
 
 struct ftlm_group {
   std::shared_ptr<ftlm::Group> G;
@@ -19,14 +20,6 @@ namespace ftlm {
 
 namespace dev {
 struct PadMap;
-// One word of the rank lookup: bit k is set when rank 64 w + k is a
-// representative, base counts the representatives before the word.  One
-// 16-byte record, because a lookup is a random access: bits and base in
-// arrays of their own cost two lines each.
-struct alignas(16) RankWord {
-  uint64_t bits;
-  uint32_t base, unused;
-};
 }  // namespace dev
 
 // Irreducible-representation-independent tables of one M sector.

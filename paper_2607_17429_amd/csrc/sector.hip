@@ -96,7 +96,7 @@ __device__ __forceinline__ dev::Orbit<W, GW, PLAIN> stage_orbit(const SecArgs& a
 // against 1.53 ms with the images of all elements; the 924 labels of the
 // icosahedron: 13 us (one wave per word) against 201 us.
 template <typename W, int GW, bool PLAIN, bool TABS, bool WAVE>
-__global__ void __launch_bounds__(kOrbitThreads) k_enum(SecArgs a, uint64_t* __restrict__ bits_out) {
+__global__ void __launch_bounds__(kOrbitThreads) k_enum(SecArgs a, dev::RankWord* __restrict__ out) {
   extern __shared__ uint64_t smem_raw[];
   const uint64_t* cnt;
   const dev::Orbit<W, GW, PLAIN> o = stage_orbit<W, GW, PLAIN, TABS>(a, smem_raw, cnt);
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kOrbitThreads) k_enum(SecArgs a, uint64_t* __r
       const bool live = rank < a.D_M;
       const W x = dev::sector_unrank<W>(live ? rank : 0, a.N, a.b, a.d, a.A, cnt, a.cnt_stride);
       const uint64_t bits = __ballot(dev::is_orbit_min<W, GW, PLAIN>(x, live, o));
-      if ((threadIdx.x & 63) == 0) bits_out[w] = bits;
+      if ((threadIdx.x & 63) == 0) out[w] = dev::RankWord{(uint32_t)bits, (uint32_t)(bits >> 32), 0u};
     }
   } else {
     for (uint64_t w = t0; w < a.n_words; w += stride) {
@@ -123,20 +123,61 @@ __global__ void __launch_bounds__(kOrbitThreads) k_enum(SecArgs a, uint64_t* __r
         if (dev::is_orbit_min<W, GW, PLAIN>(x, live, o)) bits |= 1ull << k;
         x = dev::sector_next<W>(x, a.N, a.b, a.d);
       }
-      bits_out[w] = bits;
+      out[w] = dev::RankWord{(uint32_t)bits, (uint32_t)(bits >> 32), 0u};
     }
   }
 }
 
-__global__ void k_popcount(const uint64_t* __restrict__ bits, uint64_t* __restrict__ out, uint64_t n) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    out[i] = __popcll(bits[i]);
+// Representatives before each word, in place, in tiles of kRankTile words: the
+// tiles' counts, their prefix sum (scan_exclusive_u64, 1/1536 of the records),
+// then the words' own within each tile.  Building the records needs no other
+// array of the sector's size.
+constexpr int kRankItems = 4, kRankTile = kThreads * kRankItems;
+
+// Inclusive sums of one count per thread over the workgroup (s: kThreads words).
+__device__ __forceinline__ uint32_t wg_inclusive(uint32_t own, uint32_t* s) {
+  const uint32_t t = threadIdx.x;
+  s[t] = own;
+  __syncthreads();
+  for (uint32_t step = 1; step < kThreads; step <<= 1) {
+    const uint32_t add = t >= step ? s[t - step] : 0;
+    __syncthreads();
+    s[t] += add;
+    __syncthreads();
+  }
+  return s[t];
 }
 
-__global__ void k_rank_words(const uint64_t* __restrict__ bits, const uint64_t* __restrict__ base,
-                             dev::RankWord* __restrict__ out, uint64_t n) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    out[i] = dev::RankWord{bits[i], (uint32_t)base[i], 0u};
+__global__ void __launch_bounds__(kThreads) k_rank_tiles(const dev::RankWord* __restrict__ ranks, uint64_t n,
+                                                        uint64_t* __restrict__ tile_counts) {
+  __shared__ uint32_t s[kThreads];
+  const uint64_t w0 = (uint64_t)blockIdx.x * kRankTile;
+  uint32_t own = 0;
+#pragma unroll
+  for (int i = 0; i < kRankItems; ++i) {
+    const uint64_t w = w0 + i * kThreads + threadIdx.x;
+    if (w < n) own += __popcll(dev::rank_bits(ranks[w]));
+  }
+  const uint32_t sum = wg_inclusive(own, s);
+  if (threadIdx.x == kThreads - 1) tile_counts[blockIdx.x] = sum;
+}
+
+__global__ void __launch_bounds__(kThreads) k_rank_bases(dev::RankWord* __restrict__ ranks, uint64_t n,
+                                                        const uint64_t* __restrict__ tile_base) {
+  __shared__ uint32_t s[kThreads];
+  const uint64_t w0 = (uint64_t)blockIdx.x * kRankTile + (uint64_t)threadIdx.x * kRankItems;
+  uint32_t c[kRankItems], own = 0;
+#pragma unroll
+  for (int i = 0; i < kRankItems; ++i) {
+    c[i] = w0 + i < n ? __popcll(dev::rank_bits(ranks[w0 + i])) : 0;
+    own += c[i];
+  }
+  uint32_t base = (uint32_t)tile_base[blockIdx.x] + wg_inclusive(own, s) - own;
+#pragma unroll
+  for (int i = 0; i < kRankItems; ++i) {
+    if (w0 + i < n) ranks[w0 + i].base = base;
+    base += c[i];
+  }
 }
 
 template <typename W>
@@ -144,7 +185,7 @@ __global__ void __launch_bounds__(kThreads) k_extract(SecArgs a, const dev::Rank
                                                      uint64_t* __restrict__ reps) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < a.n_words; w += stride) {
-    const uint64_t m = ranks[w].bits;
+    const uint64_t m = dev::rank_bits(ranks[w]);
     if (!m) continue;
     W x = dev::sector_unrank<W>(w * 64, a.N, a.b, a.d, a.A, a.cnt, a.cnt_stride);
     uint64_t j = ranks[w].base;
@@ -281,8 +322,9 @@ __device__ __forceinline__ bool lookup(W r, const SecArgs& a, const dev::RankWor
   if (rk >= a.D_M) return false;
   const dev::RankWord w = ranks[rk >> 6];
   const int k = (int)(rk & 63);
-  idx = w.base + (uint64_t)__popcll(w.bits & ((1ull << k) - 1));
-  return (w.bits >> k) & 1;
+  const uint64_t bits = dev::rank_bits(w);
+  idx = w.base + (uint64_t)__popcll(bits & ((1ull << k) - 1));
+  return (bits >> k) & 1;
 }
 
 // The entries of a workgroup's representatives (group i0 = blockIdx.x * rb,
@@ -658,8 +700,7 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
   }
   const int64_t limit = opts ? opts->hbm_limit_bytes : 0;
   // representatives
-  DevBuf<uint64_t> rank_bits;
-  rank_bits.alloc(s.n_words);
+  s.d_ranks.alloc(s.n_words);
   // one thread per word once the words fill the device (256 CUs x 1,024
   // threads); below that one wave per word: a sector of 924 states (15 words)
   // took 200 us with 15 threads stepping through 64 labels each
@@ -670,30 +711,29 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     const unsigned grid = grid_for(by_wave ? s.n_words * 64 : s.n_words, kOrbitThreads, 8192);
     FTLM_DISPATCH_ORBIT(s.wide, s.plain(), s.gw, {
       if (by_wave && ol.tabs)
-        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, s.d_ranks.p);
       else if (by_wave)
-        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, true>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, s.d_ranks.p);
       else if (ol.tabs)
-        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, true, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, s.d_ranks.p);
       else
-        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, rank_bits.p);
+        hipLaunchKernelGGL((k_enum<W, GW, PLAIN, false, false>), dim3(grid), dim3(kOrbitThreads), ol.bytes, st, a, s.d_ranks.p);
     });
     FTLM_HIP(hipGetLastError());
   }
   {
-    DevBuf<uint64_t> tmp;
-    tmp.alloc(s.n_words);
-    hipLaunchKernelGGL(k_popcount, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, rank_bits.p, tmp.p, s.n_words);
+    const uint64_t tiles = (s.n_words + kRankTile - 1) / kRankTile;
+    DevBuf<uint64_t> tile_base;
+    tile_base.alloc(tiles);
+    hipLaunchKernelGGL(k_rank_tiles, dim3((unsigned)tiles), dim3(kThreads), 0, st, s.d_ranks.p, s.n_words, tile_base.p);
+    FTLM_HIP(hipGetLastError());
     uint64_t total = 0;
-    scan_exclusive_u64(tmp.p, tmp.p, s.n_words, &total, st);
+    scan_exclusive_u64(tile_base.p, tile_base.p, tiles, &total, st);
     if (total >= 0xFFFFFFFFull) fail(FTLM_ERR_UNSUPPORTED, "more than 2^32 - 1 representatives");
     s.n_reps = total;
-    s.d_ranks.alloc(s.n_words);
-    hipLaunchKernelGGL(k_rank_words, dim3(grid_for(s.n_words)), dim3(kThreads), 0, st, rank_bits.p, tmp.p, s.d_ranks.p,
-                       s.n_words);
+    hipLaunchKernelGGL(k_rank_bases, dim3((unsigned)tiles), dim3(kThreads), 0, st, s.d_ranks.p, s.n_words, tile_base.p);
     FTLM_HIP(hipGetLastError());
     FTLM_HIP(hipStreamSynchronize(st));
-    rank_bits.release();
   }
   a.n_reps = s.n_reps;
   s.d_reps.alloc(s.n_reps);

@@ -226,13 +226,13 @@ struct Server {
 
 // Upper bounds: orbits number at most D_M / |G| plus the labels with a
 // non-trivial stabilizer (the 1.2 margin and the constant cover those), and
-// every bond gives at most one admissible flip per direction; 16 bytes of rank
-// record per 64 labels.
+// every bond gives at most one admissible flip per direction; 12 bytes of rank
+// record per 64 labels, built in place.
 int64_t Server::estimate_sector(const Job& j, const Group& G) const {
   const long double DM = sector_dim(j.N, j.two_s, j.two_M);
   const long double reps = DM / G.order * 1.2 + 16;
   const long double flips = (long double)j.bonds.size() / 2 * (j.two_s == 1 ? 1.0 : 2.0);
-  const long double b = DM / 64 * 16 + reps * 34 + reps * flips * 8 + (1 << 20);
+  const long double b = DM / 64 * 12 + reps * 34 + reps * flips * 8 + (1 << 20);
   return (int64_t)std::min<long double>(b, 9.0e18);
 }
 

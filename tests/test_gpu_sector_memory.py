@@ -1,0 +1,42 @@
+"""Device memory of a sector: rank records of 12 bytes per 64 labels, whose
+counts are formed in place over one tile of records, several, and more than
+one level of the prefix sum."""
+import numpy as np
+import pytest
+
+from synth import clusters
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+P = pytest.importorskip("paper_2607_17429_amd")
+
+
+def sector(name, two_M, **kw):
+    cl = clusters.get(name)
+    return cl, P.Sector(cl, P.Group(cl.N, cl.gens), two_M, two_s=1, hv_mode=P.HV_ENTRIES, **kw)
+
+
+def words(S):
+    return (S.D_M + 63) // 64
+
+
+@pytest.mark.parametrize("name,two_M", [("icosahedron", 0), ("icosahedron", 12), ("ring20_C", 4), ("ring20_C", 0), ("square6x6", 12),
+                                        ("icosidodecahedron", 0)])
+def test_rank_of_every_representative(name, two_M):
+    """15, 1, 1,969, 2,887, 1.96e7 and 2.4e6 words: every representative is
+    found at its own index."""
+    _, S = sector(name, two_M)
+    reps, _, _ = S.export()
+    rep, h, idx = S.canonicalize(torch.from_numpy(reps.astype(np.int64)).cuda())
+    assert torch.equal(idx, torch.arange(S.n_reps, device="cuda"))
+    assert np.array_equal(rep.cpu().numpy(), reps.astype(np.int64)) and int(h.abs().max()) == 0
+
+
+def test_bytes_per_label():
+    """Two sectors of one cluster differ by 12 bytes per 64 labels, 26 per
+    representative (label, stabilizer id, diagonal, row pointer) and 8 per
+    entry."""
+    (_, A), (_, B) = sector("ring20_C", 0), sector("ring20_C", 4)
+    assert A.device_bytes - B.device_bytes == (12 * (words(A) - words(B)) + 26 * (A.n_reps - B.n_reps)
+                                               + 8 * (A.n_entries - B.n_entries))
