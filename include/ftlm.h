@@ -127,7 +127,12 @@ typedef struct ftlm_opts {
   int32_t user_rho_dim;     /* d of user_rho (0 = none) */
   int32_t entry_format;     /* enum ftlm_entry_format (sector creation) */
   int64_t hbm_limit_bytes;  /* 0 = no limit; builds that would exceed it fail with
-                               FTLM_ERR_OUT_OF_MEMORY before allocating */
+                               FTLM_ERR_OUT_OF_MEMORY before allocating.  Counted:
+                               the sector's labels, rank records, entries and
+                               per-representative tables, a block's metadata and irrep
+                               matrices; not counted: the group's orbit-search tables
+                               (about 2 MiB at most) and, per block, 4 bytes per 32
+                               representatives and a copy of the bonds */
   int32_t spin_flip;        /* sector creation: 1 = resolve the M = 0 sector by the global
                                spin flip F (every digit a -> d-1-a) as well, i.e. by
                                G x Z2.  Its element (g, f) acts as U(g) F^f and has index

@@ -334,7 +334,7 @@ std::unique_ptr<Block> build_block(std::shared_ptr<Sector> sec, int irrep, int r
     FTLM_HIP(hipGetLastError());
   }
   FTLM_HIP(hipStreamSynchronize(st));
-  if (opts && opts->hbm_limit_bytes > 0 && B->device_bytes() > opts->hbm_limit_bytes)
+  if (opts && opts->hbm_limit_bytes > 0 && B->limited_bytes() > opts->hbm_limit_bytes)
     fail(FTLM_ERR_OUT_OF_MEMORY, "block tables exceed the HBM limit");
   return B;
 }

@@ -80,6 +80,9 @@ struct Sector {
                      d_reps.bytes() + d_stab_id.bytes() + d_ediag.bytes() + d_row_ptr.bytes() +
                      d_entries.bytes() + d_eidx.bytes() + d_ehc.bytes() + d_bonds.bytes() + d_J.bytes());
   }
+  // what hbm_limit_bytes counts: all but the orbit-search tables, which depend
+  // on the group and not on the sector (2 MiB of masks at most)
+  int64_t limited_bytes() const { return device_bytes() - (int64_t)d_tab.bytes(); }
 };
 
 struct Block {
@@ -113,6 +116,11 @@ struct Block {
   int64_t device_bytes() const {
     return (int64_t)(d_meta.bytes() + d_lack.bytes() + d_small.bytes()) +
            sec->device_bytes();
+  }
+  // what hbm_limit_bytes counts: the metadata and the irrep's matrices, not
+  // the lack words and the copies of the bond data next to the matrices
+  int64_t limited_bytes() const {
+    return (int64_t)(d_meta.bytes() + small_bytes - (o_V - o_J)) + sec->limited_bytes();
   }
 };
 

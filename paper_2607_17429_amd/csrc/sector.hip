@@ -860,7 +860,7 @@ std::shared_ptr<Sector> build_sector(const ftlm_cluster* cl, std::shared_ptr<con
     FTLM_HIP(hipMemGetInfo(&free_b, &total_b));
     mode = ((double)n_ent * s.entry_bytes <= (double)free_b * 2.0 / 3.0) ? FTLM_HV_ENTRIES : FTLM_HV_ONTHEFLY;
   }
-  if (limit > 0 && (int64_t)(s.device_bytes() + (mode == FTLM_HV_ENTRIES ? n_ent * s.entry_bytes : 0)) > limit)
+  if (limit > 0 && (int64_t)(s.limited_bytes() + (mode == FTLM_HV_ENTRIES ? n_ent * s.entry_bytes : 0)) > limit)
     fail(FTLM_ERR_OUT_OF_MEMORY, "sector tables exceed the HBM limit");
   s.hv_mode = mode;
   if (mode == FTLM_HV_ENTRIES && n_ent) {

@@ -40,3 +40,20 @@ def test_bytes_per_label():
     (_, A), (_, B) = sector("ring20_C", 0), sector("ring20_C", 4)
     assert A.device_bytes - B.device_bytes == (12 * (words(A) - words(B)) + 26 * (A.n_reps - B.n_reps)
                                                + 8 * (A.n_entries - B.n_entries))
+
+
+@pytest.mark.parametrize("name,two_M,irrep,d", [("icosahedron", 0, 0, 1), ("dodecahedron", 0, 0, 1), ("ring20_C", 0, 0, 1)])
+def test_limit_counts_the_sector(name, two_M, irrep, d):
+    """hbm_limit counts the tables that grow with the sector and a block's
+    metadata and matrices (64 bytes of slack: the ladder products, which were
+    on the device too), not the group's search tables."""
+    cl, S = sector(name, two_M)
+    G, nb = P.Group(cl.N, cl.gens), len(cl.bonds)
+    count = ((cl.N + 1) ** 2 * 8 + 12 * words(S) + 26 * S.n_reps + 8 + 8 * S.n_entries + 16 * nb)
+    assert sector(name, two_M, hbm_limit=count)[1].n_reps == S.n_reps
+    with pytest.raises(P.FtlmError, match="OUT_OF_MEMORY"):
+        sector(name, two_M, hbm_limit=count - 1)
+    block = count + 8 * S.n_reps + 8 * d * d * (G.order + S.n_stab) + 32 * S.n_stab
+    assert P.Block(S, irrep, hbm_limit=block + 64).d_gamma == d
+    with pytest.raises(P.FtlmError, match="OUT_OF_MEMORY"):
+        P.Block(S, irrep, hbm_limit=block - 1)
