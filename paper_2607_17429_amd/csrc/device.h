@@ -196,8 +196,9 @@ __device__ __forceinline__ W image_row(const W* __restrict__ img, int nch, int r
 
 template <typename W, int GW, bool PLAIN>
 __device__ __forceinline__ W image(const Orbit<W, GW, PLAIN>& o, int g, W x) {
+  if (o.nH == 1) return image_row<W>(o.img, o.nch, 1 + g, x);  // H = {e}, T in element order
   const uint32_t th = o.split[g];
-  if (o.nH > 1) x = image_row<W>(o.img, o.nch, (int)(th & 0xffffu), x);
+  x = image_row<W>(o.img, o.nch, (int)(th & 0xffffu), x);
   return image_row<W>(o.img, o.nch, o.nH + (int)(th >> 16), x);
 }
 
@@ -214,22 +215,42 @@ __device__ __forceinline__ W digit_plane(W x, int N, int b, int sub) {
     y = (y | (y >> 16)) & 0x00000000ffffffffull;
     return (W)y;
   }
+  if (b == 3) {
+    uint64_t y = ((uint64_t)x >> sub) & 0x1249249249249249ull;
+    y = (y | (y >> 2)) & 0x10c30c30c30c30c3ull;
+    y = (y | (y >> 4)) & 0x100f00f00f00f00full;
+    y = (y | (y >> 8)) & 0x001f0000ff0000ffull;
+    y = (y | (y >> 16)) & 0x001f00000000ffffull;
+    y = (y | (y >> 32)) & 0x00000000001fffffull;
+    return (W)y;
+  }
+  if (b == 4) {
+    uint64_t y = ((uint64_t)x >> sub) & 0x1111111111111111ull;
+    y = (y | (y >> 3)) & 0x0303030303030303ull;
+    y = (y | (y >> 6)) & 0x000f000f000f000full;
+    y = (y | (y >> 12)) & 0x000000ff000000ffull;
+    y = (y | (y >> 24)) & 0x000000000000ffffull;
+    return (W)y;
+  }
   W y = 0;
   for (int k = 0; k < N; ++k) y |= ((x >> (k * b + sub)) & W(1)) << k;
   return y;
 }
 
-// The planes of a label: kept for b <= 2, formed on use above.
+// The planes of a label: kept for b <= 4, formed on use above.
 template <typename W>
 struct Planes {
-  W x, p0, p1;
+  W x, p0, p1, p2, p3;
   int N, b;
-  __device__ __forceinline__ Planes(W x_, int N_, int b_) : x(x_), N(N_), b(b_) {
+  __device__ __forceinline__ Planes(W x_, int N_, int b_) : x(x_), p1(0), p2(0), p3(0), N(N_), b(b_) {
     p0 = digit_plane<W>(x, N, b, 0);
-    p1 = b == 2 ? digit_plane<W>(x, N, b, 1) : W(0);
+    if (b > 1) p1 = digit_plane<W>(x, N, b, 1);
+    if (b > 2) p2 = digit_plane<W>(x, N, b, 2);
+    if (b > 3) p3 = digit_plane<W>(x, N, b, 3);
   }
   __device__ __forceinline__ W of(int sub) const {
-    return b <= 2 ? (sub ? p1 : p0) : digit_plane<W>(x, N, b, sub);
+    if (b > 4) return digit_plane<W>(x, N, b, sub);
+    return sub < 2 ? (sub ? p1 : p0) : sub == 2 ? p2 : p3;
   }
 };
 
@@ -247,10 +268,16 @@ __device__ __forceinline__ void ones_at(const Orbit<W, GW, PLAIN>& o, W plane, i
 #pragma unroll
       for (int w = 0; w < GW; ++w) ones[w] |= (e[0][w] | e[1][w]) | (e[2][w] | e[3][w]);
     }
-    for (; c < o.NC; ++c) {
-      const uint64_t* e = t + (c * 16 + (int)((plane >> (4 * c)) & W(15))) * GW;
+    if (c < o.NC) {
+      // up to three more, the missing ones read the (empty) mask of value 0
+      const uint64_t* e[3];
 #pragma unroll
-      for (int w = 0; w < GW; ++w) ones[w] |= e[w];
+      for (int q = 0; q < 3; ++q) {
+        const bool in = c + q < o.NC;
+        e[q] = t + (in ? (c + q) * 16 + (int)((plane >> (4 * (c + q))) & W(15)) : 0) * GW;
+      }
+#pragma unroll
+      for (int w = 0; w < GW; ++w) ones[w] |= e[0][w] | e[1][w] | e[2][w];
     }
   };
   const size_t at = (size_t)p * o.NC * 16 * GW;
@@ -304,12 +331,32 @@ __device__ __forceinline__ int pop_lowest(uint64_t (&c)[GW]) {
   return g;
 }
 
+// Groups of up to this order are searched by the images of all elements (ring
+// of 7 sites, s = 5/2, 14 elements, on-the-fly product: 80 us with the walk, 72
+// so; rings of 18 and 20 sites, 36 and 40 elements: 70 us with the walk, 160
+// and 133 by images).
+constexpr int kFewElements = 16;
+
+// Takes the flipped images into an orbit minimum: top is the largest image
+// over G, reached first by topg and by top_ties elements.
+template <typename W, int GW, bool PLAIN>
+__device__ __forceinline__ void join_flipped(const Orbit<W, GW, PLAIN>& o, W top, int topg, int top_ties, W& best,
+                                             int& bestg, int& ties) {
+  if (o.full - top < best) {
+    best = o.full - top;
+    bestg = o.G + topg;
+    ties = top_ties;
+  } else if (o.full - top == best) {
+    ties += top_ties;
+  }
+}
+
 // Orbit minimum over G (over G x Z2 with zf) and the smallest group index h
 // reaching it (U(h) a = best; index of (g, f) is f |G| + g).  Lanes that are
 // not live do no search.  ties counts the elements that reach it, which is the
-// order of the minimum's stabilizer.  The walk over positions stops when no lane of the
-// wave has more than two candidates; those left are compared as images, the
-// lowest index first, so ties (non-trivial stabilizers) go to it as well.
+// order of the minimum's stabilizer.  The walk over positions stops when no
+// lane of the wave has more than two candidates; two that are left are
+// compared as images, a tie (non-trivial stabilizer) goes to the lower index.
 // The spin flip F reverses label order (F x = full - x), so the flipped
 // images' minimum is F of the G-orbit maximum: a second set keeps that one,
 // and a G-element wins a tie with a flipped one.
@@ -323,6 +370,26 @@ __device__ __forceinline__ void orbit_min(W a, bool live, const Orbit<W, GW, PLA
     hi[w] = o.zf() ? lo[w] : 0;
   }
   const Planes<W> planes(a, o.N, o.bits());
+  if (o.G <= kFewElements) {
+    // the images of all elements, which cost less than the walk's steps
+    best = image<W, GW, PLAIN>(o, 0, a);
+    W top = best;
+    int topg = 0, top_ties = 1;
+    bestg = 0;
+    ties = 1;
+#pragma unroll 4
+    for (int g = 1; g < o.G; ++g) {
+      const W y = image<W, GW, PLAIN>(o, g, a);
+      ties = y < best ? 1 : ties + (y == best);
+      bestg = y < best ? g : bestg;
+      best = y < best ? y : best;
+      top_ties = y > top ? 1 : top_ties + (y == top);
+      topg = y > top ? g : topg;
+      top = y > top ? y : top;
+    }
+    if (o.zf()) join_flipped(o, top, topg, top_ties, best, bestg, ties);
+    return;
+  }
   auto wide = [&] { return o.zf() ? max(count<GW>(lo), count<GW>(hi)) > 2 : count<GW>(lo) > 2; };
   bool more = __any(wide());
   for (int p = 0; p < o.N && more; ++p)
@@ -333,41 +400,27 @@ __device__ __forceinline__ void orbit_min(W a, bool live, const Orbit<W, GW, PLA
       if (o.zf()) keep_if_any<GW>(hi, ones, true);
       more = __any(wide());
     }
-  best = ~W(0);
-  bestg = 0;
-  ties = 0;
-  for (int n = count<GW>(lo); __any(n > 0); --n)
-    if (n > 0) {
-      const int g = pop_lowest<GW>(lo);
-      const W y = image<W, GW, PLAIN>(o, g, a);
-      if (ties == 0 || y < best) {
-        best = y;
-        bestg = g;
-        ties = 0;
+  // one or two are left, or, past the last position, all have the same image
+  auto extreme = [&](uint64_t(&c)[GW], bool largest, W& y, int& g, int& n) {
+    n = count<GW>(c);
+    g = pop_lowest<GW>(c);
+    const int g2 = n == 2 ? pop_lowest<GW>(c) : g;
+    y = image<W, GW, PLAIN>(o, g, a);
+    const W y2 = image<W, GW, PLAIN>(o, g2, a);
+    if (n == 2 && y != y2) {
+      n = 1;
+      if (largest ? y2 > y : y2 < y) {
+        y = y2;
+        g = g2;
       }
-      ties += y == best;
     }
+  };
+  extreme(lo, false, best, bestg, ties);
   if (o.zf()) {
-    W top = 0;
-    int topg = 0, top_ties = 0;
-    for (int n = count<GW>(hi); __any(n > 0); --n)
-      if (n > 0) {
-        const int g = pop_lowest<GW>(hi);
-        const W y = image<W, GW, PLAIN>(o, g, a);
-        if (top_ties == 0 || y > top) {
-          top = y;
-          topg = g;
-          top_ties = 0;
-        }
-        top_ties += y == top;
-      }
-    if (o.full - top < best) {
-      best = o.full - top;
-      bestg = o.G + topg;
-      ties = top_ties;
-    } else if (o.full - top == best) {
-      ties += top_ties;
-    }
+    W top;
+    int topg, top_ties;
+    extreme(hi, true, top, topg, top_ties);
+    join_flipped(o, top, topg, top_ties, best, bestg, ties);
   }
 }
 
