@@ -33,8 +33,11 @@ bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && 
 //   up to 4 vectors one lane each;
 //   above, 3 vectors per lane, 4 in FP32 and FP16 where that halves the lanes
 //   (13 FP32 vectors, d = 5: 1.77 against 1.95; 7: 1.28 against 1.14, so not
-//   below 8 lanes), and 6 in FP16, whose rows are then whole 4-byte words (24
-//   vectors, d = 3: 1.40 against 1.67), where the sector is large;
+//   below 8 lanes), and 6 for more than 12 FP16 vectors, whose rows are then
+//   whole 4-byte words (24 vectors, d = 3: 1.40 against 1.67), where the sector
+//   is large (not for fewer: 2M = 8, 4.6e5 representatives, d = 4, five FP16
+//   vectors 0.54 on one lane against 0.32 on two; square 6 x 6, 1.1e5, d = 4,
+//   eight 0.19 on two against 0.14 on four);
 //   more lanes, up to 32, where the sector's representatives leave the device
 //   idle otherwise: few waves wait for one another's flips, and many lanes
 //   decode a row's flips at once (dodecahedron H_g at M = 0, 1,648
@@ -49,7 +52,7 @@ int default_lanes(const Block& b, int nvec, int dtype, bool pad) {
   if (!adjacent_ok(b) || nvec > 64) return gl;
   if (nvec * elem <= 8)
     gl = b.dg >= 5 && (pad || nvec == 1) ? 2 : 1;
-  else if (elem == 2 && nvec > 4 && b.sec->n_reps >= (1u << 16))
+  else if (elem == 2 && nvec > 12 && b.sec->n_reps >= (1u << 16))
     gl = pow2_at_least((nvec + 5) / 6);
   else if (elem < 8 && gl >= 8 && gl * 2 >= nvec)
     gl /= 2;
