@@ -318,6 +318,10 @@ std::unique_ptr<Block> build_block(std::shared_ptr<Sector> sec, int irrep, int r
     d_n.upload_async(B->n_stab, st);
     B->d_meta.alloc(sec->n_reps);
     B->d_lack.alloc((sec->n_reps + 31) / 32);
+    uint64_t fewer = 0;
+    for (int s = 0; s < ns; ++s)
+      if (B->n_stab[s] < d) fewer += sec->stab_count[s];
+    B->use_lack = sec->n_reps >= (1u << 16) && fewer * 64 <= sec->n_reps;
     if (sec->n_reps <= kRowsSmall) {
       hipLaunchKernelGGL(k_rows_small, dim3(1), dim3(1024), 0, st, sec->d_stab_id.p, (uint32_t)sec->n_reps, (uint32_t)d,
                          d_n.p, B->d_meta.p, B->d_lack.p);

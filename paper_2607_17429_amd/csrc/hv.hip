@@ -345,7 +345,7 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.rpl = vl.rpl;
     a.rpline = vl.rpl > 1 || vl.aligned ? vl.rpline : (uint32_t)b.dg;
     a.rows = vec_rows(b, vl);
-    a.lack = b.d_lack.p;
+    a.lack = b.use_lack ? b.d_lack.p : nullptr;
     a.triv_sid = s.trivial_sid;
     a.sid = s.d_stab_id.p;
     a.meta = b.d_meta.p;

@@ -88,7 +88,7 @@ struct HvArgs {
   int pad, dstride, triv_sid;
   uint32_t rpl, rpline;
   uint64_t rows;        // rows of X and Y
-  const uint32_t* lack; // block rows: rows missing before every 32nd representative (Block::d_lack)
+  const uint32_t* lack; // block rows: rows missing before every 32nd representative (Block::d_lack), or null
   const uint16_t* sid;
   const uint64_t* meta;
   const double* ediag;
@@ -284,7 +284,7 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
         // block rows: i * d minus the rows missing before representative i,
         // kept per 32 representatives; the metadata word only where one of
         // the 32 has fewer than d rows or the stabilizer is not trivial
-        const uint32_t lack = triv ? a.lack[idx >> 5] : 0x80000000u;
+        const uint32_t lack = triv && a.lack ? a.lack[idx >> 5] : 0x80000000u;
         if (lack & 0x80000000u) {
           const uint64_t m = a.meta[idx];
           sr = (int)(m >> 48);

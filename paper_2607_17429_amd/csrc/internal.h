@@ -105,6 +105,12 @@ struct Block {
   // block rows: i d_Gamma - offset(i) at i = 32 w, top bit set when one of the
   // 32 representatives has fewer than d_Gamma rows (or the count needs the bit)
   DevBuf<uint32_t> d_lack;
+  // Targets are found through d_lack where it saves time: in sectors whose
+  // metadata does not stay in the caches (from 65,536 representatives on; s =
+  // 1/2 icosidodecahedron 2M = 8, 4.6e5: 8 to 21% of the launch) and of whose
+  // groups of 32 at most half can hold a representative with fewer rows (each
+  // such target then costs two dependent reads)
+  bool use_lack = false;
   // the H.V's small tables in one array, in the order and at the 16-byte
   // aligned offsets they have in LDS, so a workgroup stages them in one copy:
   // rho^T [g][beta][gamma] = rho(g)[gamma][beta] at 0, per stabilizer {n,
