@@ -70,6 +70,10 @@ constexpr int kThreads = 256;
 // (six FP16 columns, d = 5: 2.50 against 2.73 ms with two); at 18 and 24 the
 // spills cost more than the wave gives (1.40 against 1.44 ms).
 constexpr int hv_waves(int width) { return width <= 15 ? 4 : width >= 25 && width <= 30 ? 3 : 1; }
+// The general kernels: their clamped gathers need the registers from 11 on
+// (d = 8, square 6 x 6; d = 3, four vectors on the fly: 324 us, 387 with four
+// waves).
+constexpr int hv_waves_general(int width) { return width <= 10 ? 4 : 1; }
 constexpr uint64_t kOffMask = (1ull << 48) - 1;
 constexpr uint32_t kInvalid = 0xffffffffu;
 
@@ -210,12 +214,37 @@ __device__ __forceinline__ void stage_small(const uint8_t* src, uint32_t bytes, 
   }
 }
 
+// Where the small tables are: all in LDS, all but V_S in LDS, all in memory.
+enum HvTables { kTabLds = 0, kTabV = 1, kTabMemory = 2 };
+
+// use(i, row i) for the rows 0 .. N-1 of DG elements at(i, k), with A rows read
+// ahead of the one in use and no more: left alone the compiler keeps whole
+// matrices in registers that other waves need, or reads and waits element by
+// element (fused jobs of 24 chains, d = 4 to 6: 1.2 to 1.6 times the time).
+template <int N, int DG, int A, typename At, typename Use>
+__device__ __forceinline__ void each_row(At at, Use use) {
+  double r[A + 1][DG];
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int k = 0; k < DG; ++k) r[i][k] = i < N ? at(i, k) : 0.0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i + A < N) {
+#pragma unroll
+      for (int k = 0; k < DG; ++k) r[(i + A) % (A + 1)][k] = at(i + A, k);
+    }
+    use(i, r[i % (A + 1)]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // The H.V over the representatives p = slot, slot + slot_stride, ... < p_end of
 // one column tile: lane group of GL lanes per representative (see the file text).
 // dot[j] accumulates q_j . w of this lane's column vcol + j * (column step).
 // GW > 0: flips are found on the fly (orbit search with candidate sets of GW
 // words; osearch, ocnt: its tables); GW = 0: flips come from the entry table.
-template <typename T, int DG, int VPL, int GW, int NCH, int VAR = kGeneral>
+template <typename T, int DG, int VPL, int GW, int NCH, int VAR = kGeneral, int TAB = kTabLds>
 __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
                                         const dev::Orbit<word_t<NCH>, (GW > 0 ? GW : 1), kPlain<NCH, GW>>& osearch,
                                         const uint64_t* ocnt, int tile, uint64_t slot, uint64_t slot_stride, uint64_t p_end,
@@ -320,55 +349,62 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
     // reference instead of 2.1e-16).  FP32 and FP16 storage round the sum to
     // 6e-8 and 5e-4 anyway and take the form with fewer registers (1% faster
     // in FP32; six FP16 columns, d = 5: 2.5 against 5.5 ms).
-    constexpr bool kPerFlip = sizeof(T) == 8;
+    constexpr bool kPerFlip = sizeof(T) == 8 || DG > 6;
+    // Rows of a matrix read ahead (each_row).  Trivial targets: one from LDS,
+    // two from memory (square 6 x 6, d = 8, one FP64 vector 136 us with three,
+    // 119 with two).  The others, which are few in large sectors: none in the
+    // launches of many waves (one more row there spills 6 to 14 registers more
+    // at d = 5), else the same.  The general kernels with the tables in LDS
+    // have registers to spare and leave the schedule to the compiler, over
+    // plain loops (fused jobs of one to 8 chains 3 to 15% faster so).
+    constexpr bool kPlainLoops = !ADJ && TAB == kTabLds;
+    constexpr bool kManyWaves = VAR == kAdjacent || VAR == kNarrow;
+    constexpr int kAheadR = TAB == kTabMemory ? 2 : 1;
+    constexpr int kAheadV = kManyWaves ? (TAB == kTabV && DG * VPL <= 4 ? 3 : 0) : kAheadR;
     auto accumulate = [&](const Flip& f, T (&xv)[DG][VPL]) {
       const double* R = rhoT + (size_t)f.h() * DG * DG;
       if (f.off & Flip::kTrivial) {
-        // one row (column) of rho^T ahead of the products, and no more: left
-        // alone the compiler keeps all DG x DG elements in registers
-        if constexpr (kPerFlip) {
-          double x[DG][VPL], r[2][DG];
+        if constexpr (kPlainLoops && kPerFlip) {
 #pragma unroll
-          for (int q = 0; q < DG; ++q) r[0][q] = R[q];
+          for (int be = 0; be < DG; ++be)
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) {
+              double s = 0.0;
+#pragma unroll
+              for (int q = 0; q < DG; ++q) s = fma(R[be * DG + q], (double)xv[q][j], s);
+              acc[be][j] = fma(f.c, s, acc[be][j]);
+            }
+        } else if constexpr (kPlainLoops) {
 #pragma unroll
           for (int q = 0; q < DG; ++q)
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) x[q][j] = (double)xv[q][j];
-#pragma unroll
-          for (int be = 0; be < DG; ++be) {
-            if (be + 1 < DG) {
-#pragma unroll
-              for (int q = 0; q < DG; ++q) r[(be + 1) & 1][q] = R[(be + 1) * DG + q];
-            }
-#pragma unroll
             for (int j = 0; j < VPL; ++j) {
-              double s = r[be & 1][0] * x[0][j];
+              const double x = f.c * (double)xv[q][j];
 #pragma unroll
-              for (int q = 1; q < DG; ++q) s = fma(r[be & 1][q], x[q][j], s);
-              acc[be][j] = fma(f.c, s, acc[be][j]);
+              for (int be = 0; be < DG; ++be) acc[be][j] = fma(R[be * DG + q], x, acc[be][j]);
             }
-            __builtin_amdgcn_sched_barrier(0);
-          }
+        } else if constexpr (kPerFlip) {
+          each_row<DG, DG, kAheadR>([&](int be, int q) { return R[be * DG + q]; },
+                                    [&](int be, const double (&r)[DG]) {
+#pragma unroll
+                                      for (int j = 0; j < VPL; ++j) {
+                                        double s = r[0] * (double)xv[0][j];
+#pragma unroll
+                                        for (int q = 1; q < DG; ++q) s = fma(r[q], (double)xv[q][j], s);
+                                        acc[be][j] = fma(f.c, s, acc[be][j]);
+                                      }
+                                    });
         } else {
-          double r[2][DG];
+          each_row<DG, DG, kAheadR>([&](int q, int be) { return R[be * DG + q]; },
+                                    [&](int q, const double (&r)[DG]) {
+                                      double x[VPL];
 #pragma unroll
-          for (int be = 0; be < DG; ++be) r[0][be] = R[be * DG];
+                                      for (int j = 0; j < VPL; ++j) x[j] = f.c * (double)xv[q][j];
 #pragma unroll
-          for (int q = 0; q < DG; ++q) {
-            if (q + 1 < DG) {
+                                      for (int be = 0; be < DG; ++be)
 #pragma unroll
-              for (int be = 0; be < DG; ++be) r[(q + 1) & 1][be] = R[be * DG + q + 1];
-            }
-            double x[VPL];
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) x[j] = f.c * (double)xv[q][j];
-#pragma unroll
-            for (int be = 0; be < DG; ++be) {
-#pragma unroll
-              for (int j = 0; j < VPL; ++j) acc[be][j] = fma(r[q & 1][be], x[j], acc[be][j]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
+                                        for (int j = 0; j < VPL; ++j) acc[be][j] = fma(r[be], x[j], acc[be][j]);
+                                    });
         }
       } else {
         if (ADJ && !a.pad) {
@@ -386,20 +422,31 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
           const double* Vr = Vt + (size_t)f.sr() * DG * DG + j * a.zero;
           const double* Rj = R + j * a.zero;
           double t[DG];
+          if constexpr (kPlainLoops) {
 #pragma unroll
-          for (int q = 0; q < DG; ++q) {
-            t[q] = 0.0;
+            for (int q = 0; q < DG; ++q) {
+              t[q] = 0.0;
 #pragma unroll
-            for (int k = 0; k < DG; ++k) t[q] = fma(Vr[q * DG + k], (double)xv[k][j], t[q]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+              for (int k = 0; k < DG; ++k) t[q] = fma(Vr[q * DG + k], (double)xv[k][j], t[q]);
+            }
 #pragma unroll
-          for (int be = 0; be < DG; ++be) {
-            double s = 0.0;
+            for (int be = 0; be < DG; ++be) {
+              double s = 0.0;
 #pragma unroll
-            for (int q = 0; q < DG; ++q) s = fma(Rj[be * DG + q], t[q], s);
-            acc[be][j] = fma(f.c, s, acc[be][j]);
-            __builtin_amdgcn_sched_barrier(0);
+              for (int q = 0; q < DG; ++q) s = fma(Rj[be * DG + q], t[q], s);
+              acc[be][j] = fma(f.c, s, acc[be][j]);
+            }
+          } else {
+            each_row<2 * DG, DG, kAheadV>([&](int i, int k) { return i < DG ? Vr[i * DG + k] : Rj[(i - DG) * DG + k]; },
+                                          [&](int i, const double (&r)[DG]) {
+                                            double s = 0.0;
+#pragma unroll
+                                            for (int k = 0; k < DG; ++k) s = fma(r[k], i < DG ? (double)xv[k][j] : t[k], s);
+                                            if (i < DG)
+                                              t[i] = s;
+                                            else
+                                              acc[i - DG][j] = fma(f.c, s, acc[i - DG][j]);
+                                          });
           }
         }
       }
@@ -538,6 +585,9 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
 #pragma unroll 1
           for (int jj = 0; jj < cnt; ++jj) {
             const Flip f = flip_of(jj);
+            if constexpr (!ADJ) {
+              if (!f.n()) continue;
+            }
             T xv[DG][VPL];
             gather(f, xv);
             if (f.n()) accumulate(f, xv);
@@ -612,7 +662,7 @@ __device__ __forceinline__ void hv_pass(const HvArgs<T>& a, const HvTabs& tb,
 template <typename T, int DG, int VPL, int GW, int NCH, bool LDS_TAB, bool SLDS, int VAR = kGeneral,
           bool VG = false>
 __global__ void __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(VAR == kDeep ? 1 : hv_waves(DG * VPL))))
+__attribute__((amdgpu_waves_per_eu(VAR == kDeep ? 1 : VAR == kGeneral ? hv_waves_general(DG * VPL) : hv_waves(DG * VPL))))
 k_hv(HvArgs<T> a) {
   using W = word_t<NCH>;
   extern __shared__ uint64_t smem_raw[];
@@ -642,9 +692,9 @@ k_hv(HvArgs<T> a) {
     osearch.full = (W)a.full;
   }
   if constexpr (SLDS) stage_small(a.small, a.small_bytes, (uint8_t*)sm + a.o_small);
-  if constexpr (SLDS || GW > 0) __syncthreads();
   const uint8_t* const tabs = SLDS ? (const uint8_t*)sm + a.o_small : a.small;
   const HvTabs tb = small_tabs(a, tabs, VG ? a.small : tabs);
+  if constexpr (SLDS || GW > 0) __syncthreads();
   const int lane = threadIdx.x & 63;
   const int GL = a.GL;
   const int slots_per_wave = 64 >> a.log2GL;
@@ -670,7 +720,7 @@ k_hv(HvArgs<T> a) {
   double dot[VPL];
   bool vok[VPL];
   int vcol;
-  hv_pass<T, DG, VPL, GW, NCH, VAR>(a, tb, osearch, ocnt, (int)blockIdx.y, slot, slot_stride, p_end, dot, vok,
+  hv_pass<T, DG, VPL, GW, NCH, VAR, VG ? kTabV : SLDS ? kTabLds : kTabMemory>(a, tb, osearch, ocnt, (int)blockIdx.y, slot, slot_stride, p_end, dot, vok,
                                          vcol);
   if (EPI) {
     __shared__ double red[kThreads];

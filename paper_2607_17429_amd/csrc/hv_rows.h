@@ -25,7 +25,9 @@ namespace hvk {
 //              flight per lane, a slice of adjacent rows in 16-byte loads.
 //   kDeep      kAdjacent with several flips' slices in flight per lane group,
 //              for launches of so few waves that none waits for another.
-enum HvVariant { kGeneral = 0, kAdjacent = 1, kNarrow = 2, kDeep = 3 };
+//   kFused     kAdjacent in the fused Lanczos kernel, whose workgroup has the
+//              registers of its CU to itself.
+enum HvVariant { kGeneral = 0, kAdjacent = 1, kNarrow = 2, kDeep = 3, kFused = 4 };
 
 // lanes of a launch up to which a wave seldom shares its SIMD (256 CUs x 4
 // SIMDs x 64 lanes x 2): several slices in flight per group then hide what
