@@ -332,7 +332,11 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
   // (a 6x6-torus sector has up to 324 stabilizer types)
   c.vg = !c.slds && !otf && b.o_V <= kSmallLdsBudget;
   if (c.vg) c.slds = true;
-  c.shm = base + (c.vg ? b.o_V : c.slds ? (uint32_t)small : 0);
+  // neither: the matrices are read from memory, the tables between them still
+  // go to LDS where they fit
+  const uint32_t mid = b.o_V - b.o_stab;
+  const uint32_t staged = c.vg ? b.o_V : c.slds ? (uint32_t)small : !otf && mid <= kSmallLdsBudget ? mid : 0;
+  c.shm = base + staged;
   {
     a.reps = s.d_reps.p;
     a.row_ptr = s.d_row_ptr.p;
@@ -351,7 +355,7 @@ void hv_setup(const Block& b, int nvec, int64_t ld, int gl, const VecLayout& vl,
     a.meta = b.d_meta.p;
     a.ediag = s.d_ediag.p;
     a.small = b.d_small.p;
-    a.small_bytes = c.vg ? b.o_V : b.small_bytes;
+    a.small_bytes = staged;
     a.o_small = base;
     a.o_stab = b.o_stab;
     a.o_J = b.o_J;

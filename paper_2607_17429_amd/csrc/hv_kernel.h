@@ -96,8 +96,9 @@ struct HvArgs {
   const uint16_t* sid;
   const uint64_t* meta;
   const double* ediag;
-  // small tables (Block::d_small): bytes to stage, where they go in dynamic
-  // LDS (behind the orbit search's), offsets of the tables within
+  // small tables (Block::d_small): bytes to stage (from o_stab on where the
+  // matrices stay in memory), where they go in dynamic LDS (behind the orbit
+  // search's), offsets of the tables within
   const uint8_t* small;
   uint32_t small_bytes, o_small, o_stab, o_J, o_fac, o_bonds, o_V;
   int b, dloc, nbonds;
@@ -214,7 +215,8 @@ __device__ __forceinline__ void stage_small(const uint8_t* src, uint32_t bytes, 
   }
 }
 
-// Where the small tables are: all in LDS, all but V_S in LDS, all in memory.
+// Where the small tables are: all in LDS, all but V_S in LDS, the matrices in
+// memory (the others in LDS all the same where they fit).
 enum HvTables { kTabLds = 0, kTabV = 1, kTabMemory = 2 };
 
 // use(i, row i) for the rows 0 .. N-1 of DG elements at(i, k), with A rows read
@@ -693,8 +695,20 @@ k_hv(HvArgs<T> a) {
   }
   if constexpr (SLDS) stage_small(a.small, a.small_bytes, (uint8_t*)sm + a.o_small);
   const uint8_t* const tabs = SLDS ? (const uint8_t*)sm + a.o_small : a.small;
-  const HvTabs tb = small_tabs(a, tabs, VG ? a.small : tabs);
-  if constexpr (SLDS || GW > 0) __syncthreads();
+  HvTabs tb = small_tabs(a, tabs, VG ? a.small : tabs);
+  if constexpr (!SLDS) {
+    // stabilizer data and bonds (small_bytes from o_stab on): every flip's
+    // decoding waits for three of their elements, one after the other
+    if (a.small_bytes) {
+      stage_small(a.small + a.o_stab, a.small_bytes, (uint8_t*)sm + a.o_small);
+      const uint8_t* const mid = (const uint8_t*)sm + a.o_small;
+      tb.stabf = (const double*)mid;
+      tb.Jb = (const double*)(mid + (a.o_J - a.o_stab));
+      tb.fac = (const double*)(mid + (a.o_fac - a.o_stab));
+      tb.bonds = (const int32_t*)(mid + (a.o_bonds - a.o_stab));
+    }
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int GL = a.GL;
   const int slots_per_wave = 64 >> a.log2GL;
@@ -720,8 +734,8 @@ k_hv(HvArgs<T> a) {
   double dot[VPL];
   bool vok[VPL];
   int vcol;
-  hv_pass<T, DG, VPL, GW, NCH, VAR, VG ? kTabV : SLDS ? kTabLds : kTabMemory>(a, tb, osearch, ocnt, (int)blockIdx.y, slot, slot_stride, p_end, dot, vok,
-                                         vcol);
+  constexpr int TAB = VG ? kTabV : SLDS ? kTabLds : kTabMemory;
+  hv_pass<T, DG, VPL, GW, NCH, VAR, TAB>(a, tb, osearch, ocnt, (int)blockIdx.y, slot, slot_stride, p_end, dot, vok, vcol);
   if (EPI) {
     __shared__ double red[kThreads];
     // one vector slot j at a time: lanes with equal lg hold the same column
