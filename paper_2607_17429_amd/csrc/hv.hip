@@ -17,6 +17,12 @@ namespace {
 constexpr uint32_t kSmallLdsBudget = 48 * 1024;
 constexpr uint32_t kLdsLimit = 65536 - 2048;  // dynamic LDS; 2 KiB stay for the epilogue reduction
 
+// Lanes of a launch up to which more lanes per representative are taken
+// (default_lanes): 4 x 4 torus, s = 1, 2M = 4, 3.6e4 representatives, d = 1,
+// one FP32 vector 29 us on 4 lanes, 44 on two; square 6 x 6, 2M = 20, 1.1e5
+// representatives 35 us on 4, 31 on two.
+constexpr uint64_t kFewLanes = 163840;
+
 // Whether the adjacent-column kernels can run the block (hv_setup's rule)
 bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && b.dg == b.dgp && b.dgp <= 6; }
 
@@ -32,32 +38,40 @@ bool adjacent_ok(const Block& b) { return b.sec->hv_mode != FTLM_HV_ONTHEFLY && 
 //   dodecahedron, 7.2e8 representatives: 520 against 633);
 //   up to 4 vectors one lane each;
 //   above, 3 vectors per lane, 4 in FP32 and FP16 where that halves the lanes
-//   (13 FP32 vectors, d = 5: 1.77 against 1.95; 7: 1.28 against 1.14, so not
-//   below 8 lanes), and 6 for more than 12 FP16 vectors, whose rows are then
+//   of a large sector (13 FP32 vectors, d = 5: 1.77 against 1.95; 7: 1.28
+//   against 1.14, so not below 8 lanes; s = 3/2 cuboctahedron 2M = 4, 3.2e4
+//   representatives, d = 3: 62 us against 49 with 8 lanes), and 6 for more than 12 FP16 vectors, whose rows are then
 //   whole 4-byte words (24 vectors, d = 3: 1.40 against 1.67), where the sector
 //   is large (not for fewer: 2M = 8, 4.6e5 representatives, d = 4, five FP16
 //   vectors 0.54 on one lane against 0.32 on two; square 6 x 6, 1.1e5, d = 4,
 //   eight 0.19 on two against 0.14 on four);
+//   16 lanes for 9 to 32 vectors from d = 4 on in sectors of 2e4 to 6.5e4
+//   representatives, whose targets with a non-trivial stabilizer read their
+//   matrices for every vector of a lane again (4 x 4 torus, s = 1, 2M = 4,
+//   3.6e4 representatives, 13 FP32 vectors: 96 us against 130 with 8 lanes, 142
+//   with 4; 24: 128 against 170; at 1.4e4 72 against 67, at d = 2 as fast);
 //   more lanes, up to 32, where the sector's representatives leave the device
 //   idle otherwise: few waves wait for one another's flips, and many lanes
 //   decode a row's flips at once (dodecahedron H_g at M = 0, 1,648
 //   representatives, FP64: 24 vectors 19 us against 40 with 8 lanes, one
 //   vector 19 against 36 us; 17,238 representatives, one vector: 30 us with 4
-//   lanes, 44 with one).
+//   lanes, 44 with one); up to kFewLanes lanes in all.
 int default_lanes(const Block& b, int nvec, int dtype, bool pad) {
   if (b.sec->hv_mode == FTLM_HV_ONTHEFLY)
     return nvec <= 4 ? pow2_at_least(nvec) : std::min(16, pow2_at_least((nvec + 3) / 4));
   const int elem = dtype == FTLM_F64 ? 8 : dtype == FTLM_F32 ? 4 : 2;
   int gl = nvec <= 4 ? pow2_at_least(nvec) : pow2_at_least((nvec + 2) / 3);
   if (!adjacent_ok(b) || nvec > 64) return gl;
+  const bool large = b.sec->n_reps >= (1u << 16);
   if (nvec * elem <= 8)
     gl = b.dg >= 5 && (pad || nvec == 1) ? 2 : 1;
-  else if (elem == 2 && nvec > 12 && b.sec->n_reps >= (1u << 16))
+  else if (elem == 2 && nvec > 12 && large)
     gl = pow2_at_least((nvec + 5) / 6);
-  else if (elem < 8 && gl >= 8 && gl * 2 >= nvec)
+  else if (elem < 8 && gl >= 8 && gl * 2 >= nvec && large)
     gl /= 2;
+  if (!large && b.sec->n_reps > 20000 && b.dg >= 4 && nvec > 8 && nvec <= 32) gl = std::max(gl, 16);
   if (nvec <= 32)
-    while (gl < 32 && b.sec->n_reps * (uint64_t)(2 * gl) <= kDeepLanes) gl *= 2;
+    while (gl < 32 && b.sec->n_reps * (uint64_t)(2 * gl) <= kFewLanes) gl *= 2;
   return gl;
 }
 
@@ -112,7 +126,7 @@ std::string current_arch() {
 // timed on one of them do not replace another class's.
 int size_class(uint64_t n_reps) {
   int c = 0;
-  for (uint64_t gl = 32; gl > 1 && n_reps * gl > kDeepLanes; gl /= 2) ++c;
+  for (uint64_t gl = 32; gl > 1 && n_reps * gl > kFewLanes; gl /= 2) ++c;
   return c;
 }
 
