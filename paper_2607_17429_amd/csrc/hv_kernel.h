@@ -30,18 +30,18 @@
 // Cache, and the waves that can wait for them.  Figures (MI355X, before ->
 // after one decode per flip, four waves, adjacent columns in block rows and
 // sweeps on one XCD; icosidodecahedron M = 0, 4.02e7 flips): plain product,
-// d = 5, 24 FP32 columns 3.58 -> 2.77 ms, d = 3 3.32 -> 1.69 ms; one FP64
-// column, d = 5 1.33 -> 0.65 ms; two FP32 columns 0.91 -> 0.67 ms; 24 FP16
-// columns, d = 3 3.63 -> 1.41 ms; with the Lanczos epilogue in padded rows,
-// 24 FP32 columns, d = 5 3.34 -> 2.95 ms, d = 4 2.54 -> 2.24, d = 3 1.98 ->
-// 1.76 ms, d = 1 0.85 -> 0.79 ms.
+// d = 5, 24 FP32 columns 3.51 -> 2.71 ms, d = 3 3.32 -> 1.69 ms; one FP64
+// column, d = 5 1.33 -> 0.62 ms; two FP32 columns 0.91 -> 0.67 ms; 24 FP16
+// columns, d = 3 3.64 -> 1.40 ms; with the Lanczos epilogue in padded rows,
+// 24 FP32 columns, d = 5 3.34 -> 2.85 ms, d = 4 2.54 -> 2.15, d = 3 1.98 ->
+// 1.72 ms, d = 1 0.85 -> 0.75 ms.
 // Arithmetic is FP64; FP32 and FP16 storage round once on the store.
 //
 // Flips come from the sector's entry table (target index, h, flip id; built
 // once per sector and shared by all irreps) or are found on the fly (flip,
 // orbit search over the group, rank lookup; the search's vector instructions
 // bound it: 4.6e5 representatives of the icosidodecahedron at 2M = 8, d = 4,
-// 7 FP32 vectors 1.63 ms, 9.15 ms with a walk over the group's images that
+// 7 FP32 vectors 1.55 ms, 9.15 ms with a walk over the group's images that
 // also searched for inadmissible flips).
 //
 // Lanczos epilogue (partials != nullptr): the kernel writes

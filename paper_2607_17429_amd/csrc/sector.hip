@@ -334,7 +334,7 @@ __device__ __forceinline__ bool lookup(W r, const SecArgs& a, const dev::RankWor
 // entries (a lane per representative left the lanes of short rows idle and
 // gave a sector of a few representatives to a few lanes, one flip after the
 // other).  Bound by vector instructions (78% busy; the lookup is one random
-// 16-byte read).  4.02e7 flips of the s = 1/2 icosidodecahedron at M = 0:
+// 12-byte read).  4.02e7 flips of the s = 1/2 icosidodecahedron at M = 0:
 // 2.17 ms against 4.51 ms; the icosahedron's sectors 17 us against 257 us.
 constexpr int kFillReps = 64;
 constexpr int kFillList = 4096;  // listed flips per pass (16 KiB)
