@@ -21,9 +21,11 @@ import json
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# sources that decide what the H.V kernel reads: the kernel, its launch, the
-# entry table format and the Lanczos driver that calls it
-HV_SOURCES = ("csrc/hv_kernel.h", "csrc/hv.hip", "csrc/sector.hip", "csrc/lanczos.hip")
+# sources that decide what the H.V kernel reads: the kernel, its gathers and
+# device helpers, its launch, the entry table and the block's row offsets, and
+# the Lanczos driver that calls it
+HV_SOURCES = ("csrc/hv_kernel.h", "csrc/hv_rows.h", "csrc/device.h", "csrc/hv.hip", "csrc/sector.hip", "csrc/block.hip",
+              "csrc/lanczos.hip")
 
 
 def hv_source_sha() -> str:
